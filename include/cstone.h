@@ -202,7 +202,9 @@ CSTONE_API cstone_status cstone_link_octree_by_sort(const uint64_t* leaves, size
  * outputs are then unspecified and no linking is done).
  */
 typedef struct cstone_timings {
-    float stage_ms[4];     /* keys, sort, rebalance loop, link */
+    float stage_ms[4];     /* keys, sort, rebalance loop, link (the loop's time
+                              holds the link's where the tree is written with
+                              its links, straight from the sorted keys) */
     float sort_pass_ms[8]; /* the particle-key sort (4 entries): the first top
                               pass, the two later top passes together, the
                               bucket pass, the low passes */
@@ -466,10 +468,9 @@ CSTONE_API cstone_status cstone_tune_load(const char* path);
 /* ------------------------------------------------------------------------
  * Batched builds: many independent particle sets (Sec. 4-5 for each), of
  * uneven sizes and N_crit, built from their root leaves by one sequence of
- * launches with no host synchronisation (every stage is a single launch over
- * all sets: per-tile set tables for the keys and the segmented sort, the sets'
- * cornerstone arrays kept back to back through the rebalance rounds with one
- * scan per round and per-set convergence flags, one linking pass). The
+ * launches with no host synchronisation (every stage is one or a few launches
+ * over all sets: per-tile set tables for the keys, the segmented sort and the
+ * trees, which are written with their links straight from the sorted keys). The
  * sequence can be captured once into a hipGraph and replayed. With a 9-bit
  * sort shape the segmented sort is the split sort of cstone_sort applied per
  * set (every set's first key starts a bucket); 8-bit shapes take LSD passes.
@@ -508,7 +509,7 @@ typedef struct cstone_batch_layout {
     uint64_t workspace_bytes; /* for any sort shape */
     uint64_t n_tiles;         /* sort tiles of the current shape */
     int32_t sort_variant;
-    uint32_t rounds;          /* rebalance rounds enqueued (rounds after convergence exit at once) */
+    uint32_t rounds;          /* rebalance rounds allowed */
 } cstone_batch_layout;
 
 typedef struct cstone_batch cstone_batch; /* host-side plan */
@@ -525,8 +526,9 @@ CSTONE_API cstone_status cstone_batch_get_layout(const cstone_batch* plan, cston
  * takes the autotune table's shape for its size, else the built-in one); call
  * cstone_batch_upload again afterwards. */
 CSTONE_API cstone_status cstone_batch_set_variant(cstone_batch* plan, int variant);
-/* Rebalance rounds enqueued per build, 1 .. L + 1 = 22 (the default); a set
- * whose tree needs more reports NOT_CONVERGED. Drops a captured graph. */
+/* Rebalance rounds allowed per build, 1 .. L + 1 = 22 (the default); a set
+ * whose tree needs more reports NOT_CONVERGED and holds the array after that
+ * many rounds. Drops a captured graph. */
 CSTONE_API cstone_status cstone_batch_set_rounds(cstone_batch* plan, uint32_t rounds);
 /* Copy the plan's tables into the workspace (device, layout.workspace_bytes).
  * Synchronises `stream`; needed once before building with that workspace. */

@@ -152,7 +152,7 @@ size_t cstone_build_workspace_bytes(size_t n, size_t leaf_capacity) {
     Carve c(nullptr);
     c.take<uint64_t>(n);  // unsorted keys
     c.take<uint32_t>(1);  // non-finite flag
-    c.take<uint32_t>(kLevel6Cells);  // first positions of the level-6 nodes (sort to loop)
+    c.take<TreeState>(1);  // cleared by the sort's set-up
     // the sort runs before the loop; the loop and the link share the stream
     // without a host check in between, so they get separate parts (the split
     // list of the loop is largest for n_crit = 1)
@@ -177,11 +177,10 @@ cstone_status cstone_build(const double* x, const double* y, const double* z, si
     Carve c(ws);
     uint64_t* keys = c.take<uint64_t>(n);
     uint32_t* flag = c.take<uint32_t>(1);
-    uint32_t* level6_table = c.take<uint32_t>(kLevel6Cells);
+    TreeState* tree_state = c.take<TreeState>(1);
     // the sort shape is looked up once: the key kernel's digit counts, the
     // sort's set-up and its passes must all use the same one
     const int variant = sort_resolve_variant(n);
-    uint32_t* level6 = n && sort_uses_split(n, 63, true, variant) ? level6_table : nullptr;
     void* stage_ws = static_cast<char*>(ws) + c.off;
     const size_t stage_bytes = ws_bytes - c.off;
 
@@ -221,58 +220,81 @@ cstone_status cstone_build(const double* x, const double* y, const double* z, si
                             bad_parts, &parts, hist_digits);
             if (s != CSTONE_OK) break;
             if (mark(1) != hipSuccess) { s = CSTONE_ERR_DEVICE; break; }
-            if ((s = sort_setup_from_keys(stage_ws, n, true, variant, parts, flag, level6, stream)) != CSTONE_OK) break;
+            if ((s = sort_setup_from_keys(stage_ws, n, true, variant, parts, flag,
+                                          reinterpret_cast<uint64_t*>(tree_state), sizeof(TreeState) / 8, stream)) !=
+                CSTONE_OK)
+                break;
         } else {
             hipLaunchKernelGGL(clear_word_kernel, dim3(1), dim3(1), 0, stream, flag);
             if (mark(1) != hipSuccess) { s = CSTONE_ERR_DEVICE; break; }
         }
-        // the sort reports a failed device-side wait into the same flag word,
-        // and (split sort) hands the level-6 node positions to the loop's start
+        // the sort reports a failed device-side wait into the same flag word
         s = launch_sort(keys, sorted_keys, perm, n, 63, stage_ws, stage_bytes, stream,
-                        timed && n ? pass_ev : nullptr, /*prepared=*/true, variant, flag, level6);
+                        timed && n ? pass_ev : nullptr, /*prepared=*/true, variant, flag);
         if (s != CSTONE_OK) break;
         if (mark(2) != hipSuccess) { s = CSTONE_ERR_DEVICE; break; }
         if (nl == 0) nl = 1;  // start from the root leaf {0, 8^L}
-        // the loop and the link are enqueued together; the host looks once,
-        // after the link, and only goes round again if the loop needs more rounds
-        const size_t reb_bytes = rebalance_workspace_bytes(n, n_crit, leaf_capacity);
-        void* link_ws = static_cast<char*>(stage_ws) + reb_bytes;
-        const size_t link_bytes = stage_bytes - reb_bytes;
-        RebalanceLoop loop;
-        s = loop.begin(sorted_keys, n, n_crit, leaves, nl, leaf_capacity, counts, max_iters, stage_ws, reb_bytes,
-                       stream, flag, level6);
-        if (s != CSTONE_OK) break;
-        // The link is enqueued behind the first batch of rounds (usually the
-        // last one), so one synchronisation serves both; if more rounds are
-        // needed, it runs again once, after the last batch.
-        bool finished = false, linked = false;
-        for (uint32_t batch = 0; !finished; batch = 4) {
-            if ((s = loop.enqueue(batch)) != CSTONE_OK) break;
-            if (mark(3) != hipSuccess) { s = CSTONE_ERR_DEVICE; break; }
-            if (node_keys && batch == 0) {
+        bool done = false;
+        if (tree_possible(n, max_iters)) {  // tree and links are enqueued together, and the host looks once
+            TreePass tree;
+            if (tree.run(sorted_keys, n, n_crit, leaves, nl, leaf_capacity, counts, node_keys, child, level_offsets,
+                         stage_ws, stage_bytes, tree_state, flag, stream)) {
+                if (mark(3) != hipSuccess || mark(4) != hipSuccess) { s = CSTONE_ERR_DEVICE; break; }
+                if ((s = tree.wait(&done)) != CSTONE_OK) break;
+                if (done) {
+                    *n_leaves = tree.n_leaves;
+                    if (iters_done) *iters_done = tree.rounds;
+                    host_flag = tree.input_flags;
+                }
+            }
+        }
+        if (!done) {
+            // The rounds and the link are enqueued together; the host looks
+            // once, after the link, and only goes round again if the loop
+            // needs more rounds.
+            const size_t reb_bytes = rebalance_workspace_bytes(n, n_crit, leaf_capacity);
+            void* link_ws = static_cast<char*>(stage_ws) + reb_bytes;
+            const size_t link_bytes = stage_bytes - reb_bytes;
+            RebalanceLoop loop;
+            s = loop.begin(sorted_keys, n, n_crit, leaves, nl, leaf_capacity, counts, max_iters, stage_ws, reb_bytes,
+                           stream, flag);
+            if (s != CSTONE_OK) break;
+            // The link is enqueued behind the first batch of rounds (usually the
+            // last one), so one synchronisation serves both; if more rounds are
+            // needed, it runs again once, after the last batch.
+            bool finished = false, linked = false;
+            for (uint32_t batch = 0; !finished; batch = 4) {
+                if ((s = loop.enqueue(batch)) != CSTONE_OK) break;
+                if (mark(3) != hipSuccess) { s = CSTONE_ERR_DEVICE; break; }
+                if (node_keys && batch == 0) {
+                    s = launch_link(leaves, leaf_capacity, loop.device_leaf_count(), node_keys, child, level_offsets,
+                                    link_ws, link_bytes, stream);
+                    if (s != CSTONE_OK) break;
+                    linked = true;
+                }
+                if (mark(4) != hipSuccess) { s = CSTONE_ERR_DEVICE; break; }
+                loop.wait(&finished);
+                if (!finished) linked = false;
+            }
+            if (s != CSTONE_OK) break;
+            if (node_keys && !linked && loop.status == CSTONE_OK) {  // the tree the first link saw was not the last
+                if (mark(3) != hipSuccess) { s = CSTONE_ERR_DEVICE; break; }
                 s = launch_link(leaves, leaf_capacity, loop.device_leaf_count(), node_keys, child, level_offsets,
                                 link_ws, link_bytes, stream);
                 if (s != CSTONE_OK) break;
-                linked = true;
+                if (mark(4) != hipSuccess || hipStreamSynchronize(stream) != hipSuccess) {
+                    s = CSTONE_ERR_DEVICE;
+                    break;
+                }
             }
-            if (mark(4) != hipSuccess) { s = CSTONE_ERR_DEVICE; break; }
-            loop.wait(&finished);
-            if (!finished) linked = false;
+            *n_leaves = loop.n_leaves;
+            if (iters_done) *iters_done = loop.rounds;
+            host_flag = loop.input_flags;
+            s = loop.status;
         }
-        if (s != CSTONE_OK) break;
-        if (node_keys && !linked && loop.status == CSTONE_OK) {  // the tree the first link saw was not the last
-            if (mark(3) != hipSuccess) { s = CSTONE_ERR_DEVICE; break; }
-            s = launch_link(leaves, leaf_capacity, loop.device_leaf_count(), node_keys, child, level_offsets, link_ws,
-                            link_bytes, stream);
-            if (s != CSTONE_OK) break;
-            if (mark(4) != hipSuccess || hipStreamSynchronize(stream) != hipSuccess) { s = CSTONE_ERR_DEVICE; break; }
-        }
-        *n_leaves = loop.n_leaves;
-        if (iters_done) *iters_done = loop.rounds;
-        host_flag = loop.input_flags;
         if (host_flag & ~CSTONE_FLAG_NONFINITE) { s = CSTONE_ERR_DEVICE; break; }  // the sort gave up a wait
         if (host_flag & CSTONE_FLAG_NONFINITE) { s = CSTONE_ERR_NONFINITE; break; }
-        if ((s = loop.status) != CSTONE_OK) break;
+        if (s != CSTONE_OK) break;
         if (timed) {
             for (int i = 0; i < 4; ++i)
                 if (hipEventElapsedTime(&timings->stage_ms[i], ev[i], ev[i + 1]) != hipSuccess) s = CSTONE_ERR_DEVICE;

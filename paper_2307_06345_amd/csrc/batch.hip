@@ -11,11 +11,8 @@
 //           counting the set's first radix digit;
 //   sort    one launch per digit pass over all tiles; each set has its own
 //           digit counts and look-back chain;
-//   rebalance  all sets' cornerstone arrays back to back, one decision +
-//           scan + write launch and one split-search launch per round, for
-//           L + 1 rounds (rounds after every set has converged exit at once);
-//           per-set convergence flags; per-set leaves and counts at the end;
-//   link    one count, scan, per-set base and write pass over all entries.
+//   tree    mark, scan and write launches over all sets' tiles: leaves,
+//           counts, links and results of every set.
 // With no host synchronisation and no allocation inside, the sequence is
 // captured into one hipGraph and replayed.
 #include <algorithm>
@@ -34,12 +31,14 @@ struct cstone_batch {
     std::vector<BatchSet> sets;
     std::vector<uint4> tiles;
     std::vector<uint32_t> seg_base;
+    std::vector<uint32_t> tree_tile_set;  // set of every tile of the tree pass
     std::vector<uint64_t> part_off, leaf_off, node_off;
     uint64_t n_total = 0, leaf_slots = 0, node_slots = 0;
-    uint64_t entries = 0;  // capacity of the back-to-back arrays
-    uint64_t split_capacity = 0;
     uint64_t max_set = 0;
     uint64_t max_tiles = 0;  // over all sort shapes
+    uint64_t inode_slots = 0;
+    uint64_t max_tree_tiles = 0;  // of one set
+    bool empty_sets = false;      // some set holds no particle
     int variant = 0;
     uint32_t rounds = cs::kL + 1;
     hipGraph_t graph = nullptr;
@@ -53,12 +52,14 @@ struct BatchWs {
     BatchSet* sets;
     uint4* tiles;
     uint32_t* seg_base;
-    uint32_t* flags;
+    uint32_t* tree_tile_set;
+    uint32_t* flags;     // per set, then the sort's device-wait error word
+    uint32_t* reserved;  // per set: shared slots of its internal nodes in use; cleared with the flags
     uint64_t* keys;
     void* stage;  // the sort's workspace, then the rebalance's and the link's
     size_t stage_bytes;
     size_t bytes;
-    size_t off_tiles, off_seg_base, tables_end;  // byte offsets of the plan tables (sets start at 0)
+    size_t off_tiles, off_seg_base, off_tree, tables_end;  // byte offsets of the plan tables (sets start at 0)
 };
 
 size_t stage_bytes_for(const cstone_batch& p) {
@@ -66,10 +67,7 @@ size_t stage_bytes_for(const cstone_batch& p) {
     size_t sort_max = 0;
     for (int v = 0; v < sort_variant_count(); ++v)
         sort_max = std::max(sort_max, sort_seg_workspace_bytes(p.n_total, p.max_tiles, ns, v));
-    Carve c(nullptr);
-    c.take<uint8_t>(batch_rebalance_workspace_bytes(ns, p.entries, p.split_capacity));
-    c.take<uint8_t>(link_batch_workspace_bytes(ns, p.entries));
-    return std::max(sort_max, c.off);
+    return std::max(sort_max, batch_tree_workspace_bytes(p.n_total, ns, p.tree_tile_set.size(), p.inode_slots));
 }
 
 BatchWs carve_batch(const cstone_batch& p, void* ws) {
@@ -80,22 +78,16 @@ BatchWs carve_batch(const cstone_batch& p, void* ws) {
     w.tiles = c.take<uint4>(p.max_tiles);
     w.off_seg_base = c.off;
     w.seg_base = c.take<uint32_t>(p.sets.size());
-    w.tables_end = w.off_seg_base + p.sets.size() * sizeof(uint32_t);
-    w.flags = c.take<uint32_t>(p.sets.size() + 1);  // per set, then the sort's device-wait error word
+    w.off_tree = c.off;
+    w.tree_tile_set = c.take<uint32_t>(p.tree_tile_set.size());
+    w.tables_end = w.off_tree + p.tree_tile_set.size() * sizeof(uint32_t);
+    w.flags = c.take<uint32_t>(2 * p.sets.size() + 1);
+    w.reserved = w.flags + p.sets.size() + 1;
     w.keys = c.take<uint64_t>(p.n_total);
     w.stage_bytes = stage_bytes_for(p);
     w.stage = c.take<uint8_t>(w.stage_bytes);
     w.bytes = c.off;
     return w;
-}
-
-// the rebalance workspace and, after it, the link's, inside the stage region
-void* rebalance_ws(const BatchWs& w) { return w.stage; }
-void* link_ws(const cstone_batch& p, const BatchWs& w) {
-    return static_cast<char*>(w.stage) +
-           align_up(batch_rebalance_workspace_bytes(static_cast<uint32_t>(p.sets.size()), p.entries,
-                                                    p.split_capacity),
-                    256);
 }
 
 uint64_t tiles_for(const cstone_batch& p, int variant) {
@@ -139,8 +131,8 @@ cstone_status enqueue_build(const cstone_batch& p, const double* x, const double
     const uint32_t nt = static_cast<uint32_t>(p.tiles.size());
     cstone_status st;
     uint32_t* sort_err = w.flags + ns;
-    hipLaunchKernelGGL(fill_u32_kernel, dim3((ns + 256) / 256), dim3(256), 0, stream, w.flags,
-                       static_cast<size_t>(ns) + 1, 0u);
+    hipLaunchKernelGGL(fill_u32_kernel, dim3((2 * ns + 256) / 256), dim3(256), 0, stream, w.flags,
+                       2 * static_cast<size_t>(ns) + 1, 0u);
     if (p.n_total) {
         if ((st = sort_seg_prepare(w.stage, p.n_total, nt, ns, p.variant, stream)) != CSTONE_OK) return st;
         uint32_t stride = 0, mask = 0, shift = 0;
@@ -153,14 +145,10 @@ cstone_status enqueue_build(const cstone_batch& p, const double* x, const double
             CSTONE_OK)
             return st;
     }
-    const size_t rb = batch_rebalance_workspace_bytes(ns, p.entries, p.split_capacity);
-    if ((st = launch_batch_rebalance(sorted_keys, p.n_total, w.sets, ns, p.entries, p.split_capacity, p.rounds, w.flags,
-                                     leaves, counts, reinterpret_cast<BatchResult*>(results), rebalance_ws(w), rb,
-                                     sort_err, stream)) != CSTONE_OK)
-        return st;
-    const BatchTreeView view = batch_rebalance_view(rebalance_ws(w), ns, p.entries, p.split_capacity);
-    return launch_link_batch(view, w.sets, ns, p.entries, node_keys, child, level_offsets, link_ws(p, w),
-                             link_batch_workspace_bytes(ns, p.entries), stream);
+    return launch_batch_tree(sorted_keys, p.n_total, w.sets, ns, w.tree_tile_set, p.tree_tile_set.size(), p.max_tree_tiles,
+                             p.empty_sets, p.inode_slots, p.rounds, w.flags, sort_err, w.reserved, leaves, counts,
+                             node_keys, child, level_offsets, reinterpret_cast<BatchResult*>(results), w.stage,
+                             w.stage_bytes, stream);
 }
 
 void drop_graph(cstone_batch* p) {
@@ -181,7 +169,7 @@ CSTONE_API cstone_status cstone_batch_create(const cstone_set* sets, uint32_t n_
     cstone_batch* p = new (std::nothrow) cstone_batch();
     if (!p) return CSTONE_ERR_INVALID_ARG;
     p->in.assign(sets, sets + n_sets);
-    uint64_t part = 0, leaf = 0, node = 0, entries = 0, splits = 0;
+    uint64_t part = 0, leaf = 0, node = 0, entries = 0;
     for (uint32_t s = 0; s < n_sets; ++s) {
         const cstone_set& in = sets[s];
         if (in.n_crit == 0 || !cs::box_ok(in.box) || (in.curve != CSTONE_MORTON && in.curve != CSTONE_HILBERT)) {
@@ -209,7 +197,6 @@ CSTONE_API cstone_status cstone_batch_create(const cstone_set* sets, uint32_t n_
         leaf += cap + 1;
         node += b.node_cap;
         entries += cap + 1;
-        splits += std::min<uint64_t>(cap, in.n / (static_cast<uint64_t>(in.n_crit) + 1)) + 1;
         p->max_set = std::max<uint64_t>(p->max_set, in.n);
         p->sets.push_back(b);
         p->seg_base.push_back(b.part_off);
@@ -218,14 +205,22 @@ CSTONE_API cstone_status cstone_batch_create(const cstone_set* sets, uint32_t n_
             return CSTONE_ERR_INVALID_ARG;
         }
     }
+    for (uint32_t s = 0; s < n_sets; ++s) {  // tiles of the tree's launches
+        cs::BatchSet& b = p->sets[s];
+        b.inode_off = p->inode_slots;
+        p->inode_slots += cs::tree_slots(b.n, b.n_crit, b.cap);
+        b.tree_tile0 = static_cast<uint32_t>(p->tree_tile_set.size());
+        b.tree_tiles = static_cast<uint32_t>(cs::tree_tiles(b.n));
+        p->tree_tile_set.insert(p->tree_tile_set.end(), b.tree_tiles, s);
+        p->max_tree_tiles = std::max<uint64_t>(p->max_tree_tiles, b.tree_tiles);
+        p->empty_sets = p->empty_sets || b.n == 0;
+    }
     p->part_off.push_back(part);
     p->leaf_off.push_back(leaf);
     p->node_off.push_back(node);
     p->n_total = part;
     p->leaf_slots = leaf;
     p->node_slots = node;
-    p->entries = std::max<uint64_t>(entries, 2ull * n_sets);
-    p->split_capacity = splits + 1;
     for (int v = 0; v < cs::sort_variant_count(); ++v)
         p->max_tiles = std::max<uint64_t>(p->max_tiles, cs::tiles_for(*p, v));
     {  // the autotune table's shape for a batch of this many keys, else the built-in one
@@ -290,6 +285,9 @@ CSTONE_API cstone_status cstone_batch_upload(const cstone_batch* p, void* ws, si
         CS_HIP(hipMemcpyAsync(w.seg_base, p->seg_base.data(), p->seg_base.size() * sizeof(uint32_t),
                               hipMemcpyHostToDevice, stream));
     }
+    if (!p->tree_tile_set.empty())
+        CS_HIP(hipMemcpyAsync(w.tree_tile_set, p->tree_tile_set.data(), p->tree_tile_set.size() * sizeof(uint32_t),
+                              hipMemcpyHostToDevice, stream));
     if (!p->tiles.empty())
         CS_HIP(hipMemcpyAsync(w.tiles, p->tiles.data(), p->tiles.size() * sizeof(uint4), hipMemcpyHostToDevice,
                               stream));
@@ -313,6 +311,8 @@ CSTONE_API cstone_status cstone_batch_upload_staged(const cstone_batch* p, void*
         std::memcpy(h, p->sets.data(), p->sets.size() * sizeof(BatchSet));
         std::memcpy(h + w.off_seg_base, p->seg_base.data(), p->seg_base.size() * sizeof(uint32_t));
     }
+    if (!p->tree_tile_set.empty())
+        std::memcpy(h + w.off_tree, p->tree_tile_set.data(), p->tree_tile_set.size() * sizeof(uint32_t));
     if (!p->tiles.empty()) std::memcpy(h + w.off_tiles, p->tiles.data(), p->tiles.size() * sizeof(uint4));
     if (w.tables_end) CS_HIP(hipMemcpyAsync(ws, host_stage, w.tables_end, hipMemcpyHostToDevice, stream));
     return CSTONE_OK;

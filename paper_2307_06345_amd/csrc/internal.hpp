@@ -9,9 +9,6 @@ namespace cs {
 constexpr uint32_t kKeyBlocksMax = 512;  // blocks of the plain key kernel (grid-stride beyond)
 constexpr uint32_t kKeyDigitsMax = 3;    // digits the key kernel counts at most (the split sort's top digits)
 
-// First positions of the level-6 nodes, handed from the sort to the loop's start
-constexpr uint32_t kLevel6Cells = 1u << 18;
-constexpr uint32_t kCellEmpty = 0xffffffffu;
 // flags: NULL, or a word into which CSTONE_FLAG_NONFINITE is OR-ed.
 // hist_parts: NULL, or kKeyBlocksMax rows of kKeyDigitsMax x 512 words; block b
 // stores, for d < hist_digits and every value v, the count of keys with
@@ -38,8 +35,6 @@ size_t sort_workspace_bytes(size_t n, bool with_perm);
 // err_word: NULL, or a caller word (cleared beforehand) into which the sort's
 // kernels OR their error bits (a look-back wait that gave up, a bucket-list
 // overflow), all above the public CSTONE_FLAG_* bits.
-// level6: NULL, or kLevel6Cells words set to kCellEmpty by the set-up; the
-// split sort stores there the first position of every non-empty level-6 node.
 // variant: the sort shape (sort_variant_count() of them); -1 takes the shape
 // of the autotune table for a particle-key sort of n keys (with perm, 63
 // bits), else the built-in one. A prepared sort must name the shape its
@@ -47,8 +42,7 @@ size_t sort_workspace_bytes(size_t n, bool with_perm);
 cstone_status launch_sort(const uint64_t* keys_in, uint64_t* keys_out, uint32_t* perm_out, size_t n,
                           int sig_bits, void* ws, size_t ws_bytes, hipStream_t stream,
                           hipEvent_t* pass_events = nullptr, bool prepared = false, int variant = -1,
-                          uint32_t* err_word = nullptr, uint32_t* level6 = nullptr);
-bool sort_uses_split(size_t n, int sig_bits, bool with_perm, int variant);
+                          uint32_t* err_word = nullptr);
 // clear_word: NULL, or one caller word zeroed by the same launch; variant: the
 // sort shape the passes will use
 cstone_status sort_prepare(void* ws, size_t n, bool with_perm, hipStream_t stream, uint32_t* clear_word,
@@ -62,9 +56,9 @@ void sort_key_parts(void* ws, size_t n, bool with_perm, int sig_bits, int varian
 // Set-up after the key kernel stored its parts (replaces sort_prepare in a
 // build): the counts of the digits sort_key_parts named are the sums of the
 // `parts` rows, *flag the OR of the blocks' flags, and everything sort_prepare
-// clears is cleared.
+// clears is cleared, with clear[0 .. clear_words) of the caller's.
 cstone_status sort_setup_from_keys(void* ws, size_t n, bool with_perm, int variant, uint32_t parts, uint32_t* flag,
-                                   uint32_t* level6, hipStream_t stream);
+                                   uint64_t* clear, size_t clear_words, hipStream_t stream);
 int sort_passes(size_t n, int sig_bits, bool with_perm, int variant);
 
 // ---- batched builds: many independent sets in one pass of every stage -------
@@ -84,6 +78,9 @@ struct BatchSet {
     uint64_t node_off;  // first slot of its node keys and child offsets
     uint64_t cap;       // leaf capacity
     uint64_t node_cap;  // cap + (cap - 1) / 7
+    uint64_t inode_off;   // first slot of its internal nodes in the workspace
+    uint32_t tree_tile0;  // first of its tiles in the tree pass, and their number
+    uint32_t tree_tiles;
 };
 
 // Per-set result, written on the device: leaf and node counts, rebalance
@@ -164,6 +161,69 @@ cstone_status launch_compact_octree(const uint64_t* leaves, const uint32_t* coun
                                     uint64_t* node_keys, uint32_t* parent, uint32_t* level_offsets, size_t* n_nodes,
                                     void* ws, size_t ws_bytes, hipStream_t stream);
 
+// tree.hip — the balanced tree straight from the sorted keys, and its links
+constexpr int kTreeLevels = kL;           // levels of internal nodes: 0 .. L - 1
+constexpr int kTreeRows = kTreeLevels + 1;  // per-tile counts: a row per level, and all levels together
+
+// The one set of a plain build, in the terms of a batch's sets.
+struct TreeOne {
+    uint64_t first;  // first key
+    uint32_t n, n_crit;
+    uint64_t leaf_off, cap, inode_off;
+};
+
+// State of a plain build's tree, read by the host once (zero beforehand).
+struct TreeState {
+    uint32_t reserved;     // shared slots of the list of internal nodes in use
+    uint32_t input_flags;  // copy of the caller's key-stage flag word
+    uint64_t n_leaves;     // leaves of the tree
+    uint64_t nl;           // leaves in the caller's array, 0 if the tree (or a round on the way) does not fit
+    uint64_t inter;        // from another array: bound on the leaves of every round
+    uint32_t max_diff;     // from another array: largest level difference of overlapping leaves
+    uint32_t depth;        // level of the deepest leaf
+};
+
+size_t tree_tiles(size_t n);
+size_t tree_slots(size_t n, uint32_t n_crit, size_t cap);  // of the list of internal nodes
+size_t tree_workspace_bytes(size_t n, uint32_t n_crit, size_t cap);
+// whether the tree can stand for the rounds: they run to convergence (max_iters
+// 0 or at least L + 1) and there are particles
+bool tree_possible(size_t n, uint32_t max_iters);
+
+// The whole rebalance loop of one set, and its links (unless node_keys is
+// NULL), enqueued without a host synchronisation.
+class TreePass {
+public:
+    // From the root (nl0 == 1) or, with the rounds counted from it, from the
+    // nl0 leaves in `leaves`. cleared: a zeroed state apart from ws, or NULL.
+    // False (nothing enqueued) if ws is too short.
+    bool run(const uint64_t* sorted_keys, size_t n, uint32_t n_crit, uint64_t* leaves, size_t nl0, size_t cap,
+             uint32_t* counts, uint64_t* node_keys, uint32_t* child, uint32_t* level_offsets, void* ws, size_t ws_bytes,
+             TreeState* cleared, const uint32_t* input_flags, hipStream_t stream);
+    // Synchronises. *fits false: the tree or a round on the way to it exceeds
+    // the capacity; `leaves` holds the start array unless that was the root,
+    // and the rounds have to say how far they come.
+    cstone_status wait(bool* fits);
+    size_t n_leaves = 0;
+    uint32_t rounds = 0;
+    uint32_t input_flags = 0;
+
+private:
+    bool incremental_ = false;
+    TreeState* st_ = nullptr;
+    hipStream_t stream_ = nullptr;
+};
+
+// All sets of a batch: trees, links and results. tile_set[t]: set of tile t;
+// max_tiles: tiles of the largest set; reserved: a zeroed word per set (shared slots in use).
+size_t batch_tree_workspace_bytes(size_t n_total, uint32_t n_sets, size_t n_tiles, size_t inode_slots);
+cstone_status launch_batch_tree(const uint64_t* P, size_t n_total, const BatchSet* sets, uint32_t n_sets, const uint32_t* tile_set,
+                                size_t n_tiles, size_t max_tiles, bool empty_sets, size_t inode_slots, uint32_t rounds,
+                                const uint32_t* set_flags, const uint32_t* sort_err, uint32_t* reserved,
+                                uint64_t* leaves, uint32_t* counts, uint64_t* node_keys, uint32_t* child,
+                                uint32_t* level_offsets, BatchResult* results, void* ws, size_t ws_bytes,
+                                hipStream_t stream);
+
 // rebalance.hip
 cstone_status launch_node_counts(const uint64_t* sorted_keys, size_t n, const uint64_t* leaves, size_t n_leaves,
                                  uint32_t* counts, hipStream_t stream);
@@ -187,9 +247,6 @@ struct LoopHeader {
     uint64_t final_nl;     // set by the finalize kernel: leaves (entries) of the result array
     uint32_t final_last;   // rounds behind it
     uint32_t final_code;   // 0 running, 1 converged, 2 capacity exceeded
-    uint32_t start_level;  // from the root: rounds skipped by starting at the uniform grid of this level
-    uint32_t start_fine;   // the start-level search went finer than level 3
-    uint32_t mins[kL + 1]; // least node count of every level (start-level search)
 };
 
 // ... and, after it and never copied to the host, the tile counters of every round.
@@ -206,8 +263,7 @@ class RebalanceLoop {
 public:
     cstone_status begin(const uint64_t* sorted_keys, size_t n, uint32_t n_crit, uint64_t* leaves, size_t n_leaves,
                         size_t leaf_capacity, uint32_t* counts, uint32_t max_iters, void* ws, size_t ws_bytes,
-                        hipStream_t stream, const uint32_t* input_flags,
-                        const uint32_t* level6 = nullptr);
+                        hipStream_t stream, const uint32_t* input_flags);
     // enqueue the next batch of rounds (0: the expected number) and the finalize step
     cstone_status enqueue(uint32_t rounds = 0);
     // device word holding the leaf count of the array left in `leaves`
@@ -234,30 +290,11 @@ private:
     void* ws_ = nullptr;
     LoopState* st_ = nullptr;
     bool root_ = false;
-    int start_top_ = 0;  // > 0: the loop may start at a uniform level up to this one
 };
 
 cstone_status run_rebalance(const uint64_t* sorted_keys, size_t n, uint32_t n_crit, uint64_t* leaves,
                             size_t* n_leaves, size_t leaf_capacity, uint32_t* counts, uint32_t max_iters,
                             uint32_t* iters_done, void* ws, size_t ws_bytes, hipStream_t stream);
-
-// Batched rebalance from the root of every set, all rounds enqueued at once
-// (a round after global convergence exits at once), then per-set leaves,
-// counts and results. Sets' arrays are kept back to back on the device.
-size_t batch_rebalance_workspace_bytes(uint32_t n_sets, size_t entry_capacity, size_t split_capacity);
-cstone_status launch_batch_rebalance(const uint64_t* P, size_t n_total, const BatchSet* sets, uint32_t n_sets,
-                                     size_t entry_capacity, size_t split_capacity, uint32_t rounds,
-                                     const uint32_t* set_flags, uint64_t* leaves, uint32_t* counts,
-                                     BatchResult* results, void* ws, size_t ws_bytes, const uint32_t* sort_err,
-                                     hipStream_t stream);
-// The final back-to-back arrays, for the batched link.
-struct BatchTreeView {
-    const uint64_t* K[2];
-    const uint32_t* sid[2];
-    const uint32_t* starts[2];
-    const LoopState* st;
-};
-BatchTreeView batch_rebalance_view(void* ws, uint32_t n_sets, size_t entry_capacity, size_t split_capacity);
 
 // link.hip — n_leaves_dev, if not NULL, holds the leaf count on the device
 // (then n_leaves is only an upper bound used to size grids and workspace).
@@ -265,10 +302,6 @@ size_t link_workspace_bytes(size_t n_leaves);
 cstone_status launch_link(const uint64_t* leaves, size_t n_leaves, const uint64_t* n_leaves_dev,
                           uint64_t* node_keys, uint32_t* child, uint32_t* level_offsets, void* ws, size_t ws_bytes,
                           hipStream_t stream);
-size_t link_batch_workspace_bytes(uint32_t n_sets, size_t entry_capacity);
-cstone_status launch_link_batch(const BatchTreeView& tree, const BatchSet* sets, uint32_t n_sets,
-                                size_t entry_capacity, uint64_t* node_keys, uint32_t* child,
-                                uint32_t* level_offsets, void* ws, size_t ws_bytes, hipStream_t stream);
 // steps 3-5 of Sec. 5 from unsorted node keys: sort (keys only, 64 bits), LO
 // by search, and CO (skipped if child is NULL)
 cstone_status launch_link_finish(const uint64_t* unsorted, size_t n, uint64_t* node_keys, uint32_t* child,

@@ -40,7 +40,8 @@ __global__ __launch_bounds__(256) void sort_init_kernel(uint32_t* ghist, size_t 
 // kMaxRadix / kSetupCols sums columns [j * kSetupCols, (j + 1) * kSetupCols)
 // over the parts' rows (column p * kMaxRadix + v: digit value v of pass p),
 // reading whole row segments; the last block ORs the blocks' flags into *flag;
-// all blocks clear what sort_init_kernel clears (but the counts summed here).
+// all blocks clear what sort_init_kernel clears (but the counts summed here),
+// and clear[0 .. clear_words) for a later stage.
 constexpr uint32_t kSetupCols = kWave;
 constexpr uint32_t kSetupGroups = kKeyBlocksMax / kSetupCols;  // row groups of a summing block
 __global__ __launch_bounds__(kKeyBlocksMax) void sort_setup_kernel(uint32_t* ghist, size_t ghist_words, uint32_t* err,
@@ -48,14 +49,14 @@ __global__ __launch_bounds__(kKeyBlocksMax) void sort_setup_kernel(uint32_t* ghi
                                                                   const uint32_t* __restrict__ parts, uint32_t nparts,
                                                                   uint32_t radix, uint32_t digits,
                                                                   const uint32_t* __restrict__ bad,
-                                                                  uint32_t* flag, uint32_t* level6) {
+                                                                  uint32_t* flag, uint64_t* clear,
+                                                                  size_t clear_words) {
     __shared__ uint32_t red[kKeyBlocksMax];
     const uint32_t tid = threadIdx.x;
     const size_t t = static_cast<size_t>(blockIdx.x) * blockDim.x + tid;
     const size_t stride = static_cast<size_t>(gridDim.x) * blockDim.x;
     for (size_t i = t; i < lb_words; i += stride) lb[i] = 0;
-    if (level6)
-        for (size_t i = t; i < kLevel6Cells; i += stride) level6[i] = kCellEmpty;
+    for (size_t i = t; i < clear_words; i += stride) clear[i] = 0;
     for (size_t i = digits * radix + t; i < ghist_words; i += stride) ghist[i] = 0;
     const uint32_t sums = digits * kMaxRadix / kSetupCols;
     const uint32_t j = blockIdx.x;
@@ -613,12 +614,6 @@ struct LocalSmem {
     uint32_t first, last, end, run_end, slot, tile0, nb, maxb, next_set;
 };
 
-__device__ __forceinline__ uint32_t wave_min_u32(uint32_t v) {
-#pragma unroll
-    for (int d = kWave / 2; d >= 1; d >>= 1) v = min(v, static_cast<uint32_t>(__shfl_xor(v, d, kWave)));
-    return v;
-}
-
 __device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
 #pragma unroll
     for (int d = kWave / 2; d >= 1; d >>= 1) v = max(v, static_cast<uint32_t>(__shfl_xor(v, d, kWave)));
@@ -916,9 +911,6 @@ __device__ __forceinline__ void list_large(const LargeList& L, uint32_t start, u
 // the run-end search) it uses only for prefixes, which sorting inside a bucket
 // leaves unchanged at every position.
 //
-// level6 (NULL, or kLevel6Cells words set to kCellEmpty): the first position
-// of every non-empty level-6 node (key >> 45), found with the bucket starts.
-//
 // SEG: the keys are n_sets key sets back to back, set s starting at
 // seg_base[s] (non-decreasing), each ordered by prefix on its own; every set's
 // first key starts a bucket and no bucket runs past its set. chunk_set[b] is
@@ -926,7 +918,7 @@ __device__ __forceinline__ void list_large(const LargeList& L, uint32_t start, u
 // 1 + b] where that set starts (n if none).
 template <int BITS, int BLOCK, int ITEMS, bool SEG>
 __global__ __launch_bounds__(BLOCK, kLocalBlocksPerCU * BLOCK / (4 * kWave)) void local_sort_kernel(
-    uint64_t* keys, uint32_t* vals, uint32_t n, uint32_t pshift, LargeList large, uint32_t* err, uint32_t* level6,
+    uint64_t* keys, uint32_t* vals, uint32_t n, uint32_t pshift, LargeList large, uint32_t* err,
     const uint32_t* seg_base, uint32_t n_sets, const uint32_t* chunk_set) {
     const uint64_t* kin = keys;
     const uint32_t* vin = vals;
@@ -1021,9 +1013,6 @@ __global__ __launch_bounds__(BLOCK, kLocalBlocksPerCU * BLOCK / (4 * kWave)) voi
             const uint64_t pp = j ? sm.keys[j - 1] >> pshift : before;
             st = pj != pp;
             if constexpr (SEG) st = st || ((sm.setbits[j >> 5] >> (j & 31u)) & 1u);
-            // a level-6 node starts here too if the key's top 18 bits changed
-            const uint32_t up = 45u - pshift;
-            if (st && j < own && level6 && (pj >> up) != (pp >> up)) level6[pj >> up] = lo + j;
         }
         const uint64_t in_chunk = __ballot(st && j < own), past = __ballot(st && j >= own);
         const uint32_t base = static_cast<uint32_t>(i) * BLOCK + wave0;
@@ -1319,7 +1308,7 @@ void sort_key_parts(void* ws, size_t n, bool with_perm, int sig_bits, int varian
 }
 
 cstone_status sort_setup_from_keys(void* ws, size_t n, bool with_perm, int variant, uint32_t parts, uint32_t* flag,
-                                   uint32_t* level6, hipStream_t stream) {
+                                   uint64_t* clear, size_t clear_words, hipStream_t stream) {
     if (!with_perm || parts == 0 || parts > kKeyBlocksMax) return CSTONE_ERR_INVALID_ARG;
     if (variant < 0 || variant >= kNumVariants) return CSTONE_ERR_INVALID_ARG;
     SortWs s = carve_sort(ws, n, with_perm);
@@ -1334,13 +1323,9 @@ cstone_status sort_setup_from_keys(void* ws, size_t n, bool with_perm, int varia
     const uint32_t grid = std::max<uint32_t>(digits * kMaxRadix / kSetupCols + 1, kMaxRadix + 1);
     hipLaunchKernelGGL(sort_setup_kernel, dim3(grid), dim3(kKeyBlocksMax), 0, stream, s.ghist,
                        static_cast<size_t>(kGhistWords), s.err, static_cast<uint64_t*>(s.lb), lb_words, s.key_parts,
-                       parts, radix, digits, s.key_bad, flag, level6);
+                       parts, radix, digits, s.key_bad, flag, clear, clear_words);
     CS_HIP(hipGetLastError());
     return CSTONE_OK;
-}
-
-bool sort_uses_split(size_t n, int sig_bits, bool with_perm, int variant) {
-    return use_split(n, sig_bits, with_perm, variant_or_builtin(variant));
 }
 
 namespace {
@@ -1350,7 +1335,7 @@ namespace {
 // listed buckets keys_out -> alt -> ... -> keys_out.
 cstone_status launch_split(const uint64_t* keys_in, uint64_t* keys_out, uint32_t* perm_out, size_t n,
                            const SortWs& s, const Variant& var, bool wide, hipStream_t stream,
-                           hipEvent_t* pass_events, uint32_t* err, uint32_t* level6, bool top_counted) {
+                           hipEvent_t* pass_events, uint32_t* err, bool top_counted) {
     constexpr int radix = 1 << kSplitBits;
     uint32_t* lb32[2] = {static_cast<uint32_t*>(s.lb), static_cast<uint32_t*>(s.lb) + s.rows * kMaxRadix};
     if (pass_events) CS_HIP(hipEventRecord(pass_events[0], stream));
@@ -1399,7 +1384,7 @@ cstone_status launch_split(const uint64_t* keys_in, uint64_t* keys_out, uint32_t
     const uint32_t chunks = static_cast<uint32_t>((n + kLocalChunk - 1) / kLocalChunk);
     hipLaunchKernelGGL((local_sort_kernel<kSplitBits, kLocalBlock, kLocalItems, false>), dim3(chunks),
                        dim3(kLocalBlock), 0, stream, keys_out, perm_out, static_cast<uint32_t>(n), kSplitShift, L, err,
-                       level6, static_cast<const uint32_t*>(nullptr), 0u, static_cast<const uint32_t*>(nullptr));
+                       static_cast<const uint32_t*>(nullptr), 0u, static_cast<const uint32_t*>(nullptr));
     if (pass_events) CS_HIP(hipEventRecord(pass_events[3], stream));
     if (s.max_buckets > 0) {  // some bucket may be longer than one block sorts
         hipLaunchKernelGGL(large_hist_kernel, dim3(std::min(L.max_tiles, kListGrid)), dim3(512), 0, stream, keys_out,
@@ -1434,7 +1419,7 @@ cstone_status launch_split(const uint64_t* keys_in, uint64_t* keys_out, uint32_t
 
 cstone_status launch_sort(const uint64_t* keys_in, uint64_t* keys_out, uint32_t* perm_out, size_t n,
                           int sig_bits, void* ws, size_t ws_bytes, hipStream_t stream, hipEvent_t* pass_events,
-                          bool prepared, int variant, uint32_t* err_word, uint32_t* level6) {
+                          bool prepared, int variant, uint32_t* err_word) {
     const bool with_perm = perm_out != nullptr;
     SortWs s = carve_sort(ws, n, with_perm);
     if (ws_bytes < s.bytes) return CSTONE_ERR_INVALID_ARG;
@@ -1461,7 +1446,7 @@ cstone_status launch_sort(const uint64_t* keys_in, uint64_t* keys_out, uint32_t*
     }
     uint32_t* err = err_word ? err_word : s.err;
     if (split)
-        return launch_split(keys_in, keys_out, perm_out, n, s, var, wide, stream, pass_events, err, level6, prepared);
+        return launch_split(keys_in, keys_out, perm_out, n, s, var, wide, stream, pass_events, err, prepared);
 
     uint32_t* lb32[2] = {static_cast<uint32_t*>(s.lb), static_cast<uint32_t*>(s.lb) + s.rows * kMaxRadix};
     if (pass_events) CS_HIP(hipEventRecord(pass_events[0], stream));
@@ -1666,7 +1651,7 @@ cstone_status launch_split_seg(const uint64_t* keys_in, uint64_t* keys_out, uint
     L.wide = wide ? 1u : 0u;
     hipLaunchKernelGGL((local_sort_kernel<kSplitBits, kLocalBlock, kLocalItems, true>), dim3(chunks),
                        dim3(kLocalBlock), 0, stream, keys_out, perm_out, static_cast<uint32_t>(n_total), kSplitShift,
-                       L, err, static_cast<uint32_t*>(nullptr), seg_base, n_sets,
+                       L, err, seg_base, n_sets,
                        static_cast<const uint32_t*>(s.chunk_set));
     if (s.max_buckets > 0) {  // some bucket may be longer than one block sorts
         hipLaunchKernelGGL(large_hist_kernel, dim3(std::min(L.max_tiles, kListGrid)), dim3(512), 0, stream, keys_out,
