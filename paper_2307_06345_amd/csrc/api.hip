@@ -220,7 +220,7 @@ cstone_status cstone_build(const double* x, const double* y, const double* z, si
                             bad_parts, &parts, hist_digits);
             if (s != CSTONE_OK) break;
             if (mark(1) != hipSuccess) { s = CSTONE_ERR_DEVICE; break; }
-            if ((s = sort_setup_from_keys(stage_ws, n, true, variant, parts, flag,
+            if ((s = sort_setup_from_keys(stage_ws, n, true, variant, parts, keys, flag,
                                           reinterpret_cast<uint64_t*>(tree_state), sizeof(TreeState) / 8, stream)) !=
                 CSTONE_OK)
                 break;

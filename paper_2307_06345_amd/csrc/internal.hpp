@@ -7,7 +7,7 @@ namespace cs {
 
 // keys.hip
 constexpr uint32_t kKeyBlocksMax = 512;  // blocks of the plain key kernel (grid-stride beyond)
-constexpr uint32_t kKeyDigitsMax = 3;    // digits the key kernel counts at most (the split sort's top digits)
+constexpr uint32_t kKeyDigitsMax = 4;    // digits the key kernel counts at most (the split sort's)
 
 // flags: NULL, or a word into which CSTONE_FLAG_NONFINITE is OR-ed.
 // hist_parts: NULL, or kKeyBlocksMax rows of kKeyDigitsMax x 512 words; block b
@@ -49,16 +49,17 @@ cstone_status sort_prepare(void* ws, size_t n, bool with_perm, hipStream_t strea
                            int variant);
 // Per-block digit counts and non-finite flags of the key kernel, in the sort
 // workspace: where to store them and which digits to count (the first pass's
-// digit, or for the split sort its three top digits: a histogram does not
-// depend on the order of the keys, so the unsorted keys give every pass's).
+// digit, or for the split sort its three top digits and the one below them: a
+// histogram does not depend on the order of the keys, so the unsorted keys give
+// every pass's).
 void sort_key_parts(void* ws, size_t n, bool with_perm, int sig_bits, int variant, uint32_t** hist_parts,
                     uint32_t** bad_parts, uint32_t* mask, uint32_t* shift, uint32_t* digits);
 // Set-up after the key kernel stored its parts (replaces sort_prepare in a
 // build): the counts of the digits sort_key_parts named are the sums of the
 // `parts` rows, *flag the OR of the blocks' flags, and everything sort_prepare
 // clears is cleared, with clear[0 .. clear_words) of the caller's.
-cstone_status sort_setup_from_keys(void* ws, size_t n, bool with_perm, int variant, uint32_t parts, uint32_t* flag,
-                                   uint64_t* clear, size_t clear_words, hipStream_t stream);
+cstone_status sort_setup_from_keys(void* ws, size_t n, bool with_perm, int variant, uint32_t parts, const uint64_t* keys,
+                                   uint32_t* flag, uint64_t* clear, size_t clear_words, hipStream_t stream);
 int sort_passes(size_t n, int sig_bits, bool with_perm, int variant);
 
 // ---- batched builds: many independent sets in one pass of every stage -------

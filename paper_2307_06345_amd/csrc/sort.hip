@@ -23,16 +23,77 @@ constexpr int kMaxPasses = 8;
 constexpr int kHistBlock = 256;
 constexpr int kMinTile = 2048;  // smallest tile of any variant (sizes the look-back rows)
 
+// lb2: NULL, or the second set of look-back rows (cleared as far as the first).
 __global__ __launch_bounds__(256) void sort_init_kernel(uint32_t* ghist, size_t ghist_words, uint32_t* err,
-                                                        uint64_t* lb, size_t lb_words, uint32_t* extra) {
+                                                        uint64_t* lb, uint64_t* lb2, size_t lb_words, uint32_t* extra) {
     const size_t t = static_cast<size_t>(blockIdx.x) * blockDim.x + threadIdx.x;
     const size_t stride = static_cast<size_t>(gridDim.x) * blockDim.x;
-    for (size_t i = t; i < lb_words; i += stride) lb[i] = 0;  // flag 0: not yet written
+    for (size_t i = t; i < lb_words; i += stride) {
+        lb[i] = 0;  // flag 0: not yet written
+        if (lb2) lb2[i] = 0;
+    }
     for (size_t i = t; i < ghist_words; i += stride) ghist[i] = 0;
     if (t == 0) {
         *err = 0;
         if (extra) *extra = 0;  // a caller's word cleared along the way
     }
+}
+
+// ---- depth of the split -------------------------------------------------------
+//
+// The split sort's three top digits leave buckets of one 27-bit prefix. Where
+// many keys share theirs with hundreds of others (a cluster's core), the bucket
+// kernel and the low passes over listed buckets cost more than one more digit
+// pass below the top ones, after which the buckets are those of one 36-bit
+// prefix. The size of the bucket that a key finds itself in, on average over
+// the keys, tells: n times the share of pairs of keys with one prefix, which a
+// sample of kDeepSample keys estimates (drawn at scattered places: keys in
+// curve order would hide it from an even stride). One block counts the pairs in
+// a hash table in LDS and sets the word that the passes read; nothing returns
+// to the host.
+constexpr uint32_t kDeepSample = 2048;
+constexpr uint32_t kDeepSlots = 4096;  // twice the sample
+// Mean bucket from which the extra digit pays. Sorts of Plummer keys, three top
+// digits against four: 2^18 keys (mean 6.5) 101 / 109 us, 2^20 (23) 154 / 136,
+// 2^22 (89) 255 / 207, 2^24 (354) 742 / 581, 2^27 (2828) 6149 / 3985; uniform
+// 2^24 (1.1) 468 / 568.
+constexpr uint32_t kDeepBucket = 16;
+constexpr uint32_t kDeepPairs = 4;  // fewer pairs in the sample may be chance
+constexpr uint32_t kDeepMinKeys = 1u << 20;  // shorter sorts gain less than the extra launch costs where it is left out
+
+// All threads of the block (blockDim.x divides kDeepSample); slots, pairs: LDS.
+__device__ __forceinline__ void decide_depth(const uint64_t* __restrict__ keys, uint32_t n, uint32_t* slots,
+                                             uint32_t* pairs, uint32_t* deep) {
+    for (uint32_t i = threadIdx.x; i < kDeepSlots; i += blockDim.x) slots[i] = 0;
+    if (threadIdx.x == 0) *pairs = 0;
+    __syncthreads();
+    uint32_t mine = 0;
+    for (uint32_t i = threadIdx.x; i < kDeepSample; i += blockDim.x) {
+        // one place in each of kDeepSample equal shares of the keys, scattered
+        // within it by a multiplicative hash of the share's number
+        const uint64_t a = static_cast<uint64_t>(n) * i / kDeepSample;
+        const uint64_t len = static_cast<uint64_t>(n) * (i + 1) / kDeepSample - a;
+        const uint64_t at = a + ((static_cast<uint64_t>(i * 2654435761u) * len) >> 32);
+        // word: prefix + 1 (0 is free) << 4, and the keys seen with it, counted up to 15
+        const uint32_t tag = (static_cast<uint32_t>(keys[at] >> 36) + 1u) << 4;
+        for (uint32_t s = (tag * 2654435761u) >> 20;; s = (s + 1) & (kDeepSlots - 1)) {  // the table is half empty
+            const uint32_t old = atomicCAS(&slots[s], 0u, tag | 1u);
+            if (old == 0) break;
+            if ((old & ~15u) == tag) {
+                const uint32_t seen = old & 15u;
+                mine += seen;
+                if (seen < 15u) atomicCAS(&slots[s], old, old + 1u);
+                break;
+            }
+        }
+    }
+    atomicAdd(pairs, mine);
+    __syncthreads();
+    if (threadIdx.x == 0)
+        *deep = *pairs >= kDeepPairs &&
+                        2ull * *pairs * n >= static_cast<uint64_t>(kDeepBucket) * kDeepSample * kDeepSample
+                    ? 1u
+                    : 0u;
 }
 
 // Set-up of a build's sort from the key kernel's per-block parts (rows of
@@ -41,23 +102,32 @@ __global__ __launch_bounds__(256) void sort_init_kernel(uint32_t* ghist, size_t 
 // over the parts' rows (column p * kMaxRadix + v: digit value v of pass p),
 // reading whole row segments; the last block ORs the blocks' flags into *flag;
 // all blocks clear what sort_init_kernel clears (but the counts summed here),
-// and clear[0 .. clear_words) for a later stage.
+// and clear[0 .. clear_words) for a later stage. deep: NULL, or the word (among
+// the cleared ones) that says whether a split sort of the n keys takes its
+// extra digit; one block decides it.
 constexpr uint32_t kSetupCols = kWave;
 constexpr uint32_t kSetupGroups = kKeyBlocksMax / kSetupCols;  // row groups of a summing block
 __global__ __launch_bounds__(kKeyBlocksMax) void sort_setup_kernel(uint32_t* ghist, size_t ghist_words, uint32_t* err,
-                                                                  uint64_t* lb, size_t lb_words,
+                                                                  uint64_t* lb, uint64_t* lb2, size_t lb_words,
                                                                   const uint32_t* __restrict__ parts, uint32_t nparts,
                                                                   uint32_t radix, uint32_t digits,
                                                                   const uint32_t* __restrict__ bad,
                                                                   uint32_t* flag, uint64_t* clear,
-                                                                  size_t clear_words) {
-    __shared__ uint32_t red[kKeyBlocksMax];
+                                                                  size_t clear_words, const uint64_t* __restrict__ keys,
+                                                                  uint32_t n, uint32_t* deep) {
+    __shared__ uint32_t red[kDeepSlots];
+    __shared__ uint32_t pairs;
+    static_assert(kKeyBlocksMax <= kDeepSlots, "shared by the sums and the depth's table");
     const uint32_t tid = threadIdx.x;
     const size_t t = static_cast<size_t>(blockIdx.x) * blockDim.x + tid;
     const size_t stride = static_cast<size_t>(gridDim.x) * blockDim.x;
-    for (size_t i = t; i < lb_words; i += stride) lb[i] = 0;
+    for (size_t i = t; i < lb_words; i += stride) {
+        lb[i] = 0;
+        if (lb2) lb2[i] = 0;
+    }
     for (size_t i = t; i < clear_words; i += stride) clear[i] = 0;
-    for (size_t i = digits * radix + t; i < ghist_words; i += stride) ghist[i] = 0;
+    for (size_t i = digits * radix + t; i < ghist_words; i += stride)
+        if (ghist + i != deep) ghist[i] = 0;
     const uint32_t sums = digits * kMaxRadix / kSetupCols;
     const uint32_t j = blockIdx.x;
     if (j < sums) {  // block-uniform
@@ -89,22 +159,44 @@ __global__ __launch_bounds__(kKeyBlocksMax) void sort_setup_kernel(uint32_t* ghi
             *flag = any ? CSTONE_FLAG_NONFINITE : 0u;
             *err = 0;
         }
+    } else if (j == sums + 1 && deep) {  // block-uniform: the split's depth
+        if (n >= kDeepMinKeys)
+            decide_depth(keys, n, red, &pairs, deep);
+        else if (tid == 0)
+            *deep = 0;
     }
 }
 
-// Counts of the first pass's digit ((key >> shift) & mask, mask = radix - 1).
+// Counts of the first pass's digit ((key >> shift) & mask, mask = radix - 1)
+// into ghist. deep: NULL, or a split sort's depth word, which the grid's last
+// block decides while the others also count the digit above (for the pass that
+// is the first where the extra one is left out).
 __global__ __launch_bounds__(kHistBlock) void sort_hist0_kernel(const uint64_t* __restrict__ keys, uint32_t n,
-                                                                 uint32_t shift, uint32_t mask,
-                                                                 uint32_t* __restrict__ ghist) {
-    __shared__ uint32_t h[kMaxRadix];
-    for (int i = threadIdx.x; i < kMaxRadix; i += kHistBlock) h[i] = 0;
+                                                                 uint32_t shift, uint32_t mask, uint32_t bits,
+                                                                 uint32_t* __restrict__ ghist, uint32_t* deep) {
+    __shared__ uint32_t h[kDeepSlots];
+    __shared__ uint32_t pairs;
+    static_assert(2 * kMaxRadix <= kDeepSlots, "shared by the counts and the depth's table");
+    const uint32_t blocks = deep ? gridDim.x - 1 : gridDim.x;
+    if (blockIdx.x == blocks) {  // block-uniform
+        if (n >= kDeepMinKeys)
+            decide_depth(keys, n, h, &pairs, deep);
+        return;  // (the word is cleared)
+    }
+    const uint32_t words = deep ? 2 * kMaxRadix : kMaxRadix;
+    for (uint32_t i = threadIdx.x; i < words; i += kHistBlock) h[i] = 0;
     __syncthreads();
-    const uint32_t stride = gridDim.x * kHistBlock;
-    for (uint32_t i = blockIdx.x * kHistBlock + threadIdx.x; i < n; i += stride)
-        atomicAdd(&h[static_cast<uint32_t>(keys[i] >> shift) & mask], 1u);
+    const uint32_t stride = blocks * kHistBlock;
+    for (uint32_t i = blockIdx.x * kHistBlock + threadIdx.x; i < n; i += stride) {
+        const uint64_t k = keys[i] >> shift;
+        atomicAdd(&h[static_cast<uint32_t>(k) & mask], 1u);
+        if (deep) atomicAdd(&h[kMaxRadix + (static_cast<uint32_t>(k >> bits) & mask)], 1u);
+    }
     __syncthreads();
-    for (int i = threadIdx.x; i <= static_cast<int>(mask); i += kHistBlock)
+    for (uint32_t i = threadIdx.x; i <= mask; i += kHistBlock) {
         if (h[i]) atomicAdd(&ghist[i], h[i]);
+        if (deep && h[kMaxRadix + i]) atomicAdd(&ghist[mask + 1 + i], h[kMaxRadix + i]);
+    }
 }
 
 // Look-back words. 32-bit: [31:30] flag, [29:0] value (n < 2^30), cleared
@@ -237,11 +329,15 @@ __device__ __forceinline__ uint32_t tile_of_block(uint32_t b, uint32_t nblocks) 
     return (r * 8u + q % 8u) * kXcdGroup + q / 8u;
 }
 
+// Where a pass's permutation values come from: vals_in, the keys' own places,
+// or (the split sort's first certain pass) either, as the depth word says.
+constexpr int kLater = 0, kFirst = 1, kEither = 2;
+
 struct TileDesc {
     uint32_t tile, base, count, first, seg_base;
 };
 
-template <int BITS, int BLOCK, int ITEMS, int WIN, bool FIRST, bool WITH_VALUES, class LB, bool FULL>
+template <int BITS, int BLOCK, int ITEMS, int WIN, int MODE, bool WITH_VALUES, class LB, bool FULL>
 __device__ __forceinline__ void onesweep_tile(const TileDesc td, const uint64_t* __restrict__ keys_in,
                                               const uint32_t* __restrict__ vals_in, uint64_t* __restrict__ keys_out,
                                               uint32_t* __restrict__ vals_out, uint32_t n, uint32_t shift,
@@ -249,7 +345,7 @@ __device__ __forceinline__ void onesweep_tile(const TileDesc td, const uint64_t*
                                               uint32_t shift_next, typename LB::word* lb, uint32_t epoch,
                                               uint32_t* err, uint64_t* stage, uint16_t (*whist)[1 << BITS],
                                               uint32_t* nhist, uint32_t* ddelta, uint64_t* scan_tmp,
-                                              const uint4* __restrict__ table) {
+                                              const uint4* __restrict__ table, bool own_places = MODE == kFirst) {
     constexpr int RADIX = 1 << BITS;
     constexpr int W = BLOCK / kWave;
     constexpr int TILE = BLOCK * ITEMS;
@@ -336,10 +432,10 @@ __device__ __forceinline__ void onesweep_tile(const TileDesc td, const uint64_t*
     // (not earlier: the keys must be dead by then to keep the registers in budget)
     __builtin_amdgcn_sched_barrier(0);
     uint32_t v[ITEMS];
-    if constexpr (WITH_VALUES && FIRST) {
+    if (WITH_VALUES && (MODE == kFirst || (MODE == kEither && own_places))) {  // block-uniform
 #pragma unroll
         for (int i = 0; i < ITEMS; ++i) v[i] = wave_base + i * kWave + lane - td.seg_base;
-    } else if constexpr (WITH_VALUES) {
+    } else if constexpr (WITH_VALUES && MODE != kFirst) {
         const uint32_t* vp = vals_in + (wave_base + lane);
 #pragma unroll
         for (int i = 0; i < ITEMS; ++i) {
@@ -435,7 +531,7 @@ __device__ __forceinline__ void onesweep_tile(const TileDesc td, const uint64_t*
 }
 
 
-template <int BITS, int BLOCK, int ITEMS, int WIN, bool FIRST, bool WITH_VALUES, class LB>
+template <int BITS, int BLOCK, int ITEMS, int WIN, int MODE, bool WITH_VALUES, class LB>
 __global__ __launch_bounds__(BLOCK, (kMinBlocks<BLOCK, ITEMS>)) void onesweep_kernel(const uint64_t* __restrict__ keys_in,
                                                           const uint32_t* __restrict__ vals_in,
                                                           uint64_t* __restrict__ keys_out,
@@ -443,11 +539,28 @@ __global__ __launch_bounds__(BLOCK, (kMinBlocks<BLOCK, ITEMS>)) void onesweep_ke
                                                           const uint32_t* __restrict__ ghist,
                                                           uint32_t* __restrict__ ghist_next, uint32_t shift_next,
                                                           typename LB::word* lb, typename LB::word* lb_clear,
-                                                          uint32_t epoch, uint32_t* err) {
+                                                          uint32_t epoch, uint32_t* err,
+                                                          const uint32_t* __restrict__ deep,
+                                                          const uint64_t* __restrict__ deep_keys,
+                                                          const uint32_t* __restrict__ deep_vals) {
     constexpr int RADIX = 1 << BITS;
     constexpr int W = BLOCK / kWave;
     constexpr int TILE = BLOCK * ITEMS;
     static_assert(BLOCK >= RADIX, "one digit per thread in the digit loops");
+    // kFirst with a depth word: the extra pass, left out where the word is 0.
+    // kEither: the pass after it, which reads the extra pass's output where it ran.
+    bool own_places = MODE == kFirst;
+    if (MODE != kLater && deep) {
+        const bool ran = *deep != 0;
+        if (MODE == kFirst && !ran) return;
+        if (MODE == kEither) {
+            own_places = !ran;
+            if (ran) {
+                keys_in = deep_keys;
+                vals_in = deep_vals;
+            }
+        }
+    }
     // the tile reordered by digit (keys, then values)
     __shared__ uint64_t stage[TILE];
     __shared__ uint16_t whist[W][RADIX];
@@ -462,20 +575,20 @@ __global__ __launch_bounds__(BLOCK, (kMinBlocks<BLOCK, ITEMS>)) void onesweep_ke
     const uint32_t base = tile * static_cast<uint32_t>(TILE);
     const TileDesc td{tile, base, min(n - base, static_cast<uint32_t>(TILE)), 0u, 0u};
     if (td.count == static_cast<uint32_t>(TILE))
-        onesweep_tile<BITS, BLOCK, ITEMS, WIN, FIRST, WITH_VALUES, LB, true>(
+        onesweep_tile<BITS, BLOCK, ITEMS, WIN, MODE, WITH_VALUES, LB, true>(
             td, keys_in, vals_in, keys_out, vals_out, n, shift, ghist, ghist_next, shift_next, lb, epoch, err, stage,
-            whist, nhist, ddelta, scan_tmp, nullptr);
+            whist, nhist, ddelta, scan_tmp, nullptr, own_places);
     else
-        onesweep_tile<BITS, BLOCK, ITEMS, WIN, FIRST, WITH_VALUES, LB, false>(
+        onesweep_tile<BITS, BLOCK, ITEMS, WIN, MODE, WITH_VALUES, LB, false>(
             td, keys_in, vals_in, keys_out, vals_out, n, shift, ghist, ghist_next, shift_next, lb, epoch, err, stage,
-            whist, nhist, ddelta, scan_tmp, nullptr);
+            whist, nhist, ddelta, scan_tmp, nullptr, own_places);
 }
 
 // Segmented pass: many independent key sets in one launch. Block b sorts
 // tile tiles[b] = {first key, key count, first tile of its set, set}; every
 // set has its own digit histograms (ghist + set * hist_stride) and its own
 // look-back chain, and its permutation values count from the set's start.
-template <int BITS, int BLOCK, int ITEMS, int WIN, bool FIRST, bool WITH_VALUES, class LB>
+template <int BITS, int BLOCK, int ITEMS, int WIN, int MODE, bool WITH_VALUES, class LB>
 __global__ __launch_bounds__(BLOCK, (kMinBlocks<BLOCK, ITEMS>)) void onesweep_seg_kernel(const uint64_t* __restrict__ keys_in,
                                                               const uint32_t* __restrict__ vals_in,
                                                               uint64_t* __restrict__ keys_out,
@@ -509,11 +622,11 @@ __global__ __launch_bounds__(BLOCK, (kMinBlocks<BLOCK, ITEMS>)) void onesweep_se
     const uint32_t* gh = ghist + static_cast<size_t>(t.w) * hist_stride;
     uint32_t* gn = ghist_next ? ghist_next + static_cast<size_t>(t.w) * hist_stride : nullptr;
     if (td.count == static_cast<uint32_t>(TILE))
-        onesweep_tile<BITS, BLOCK, ITEMS, WIN, FIRST, WITH_VALUES, LB, true>(
+        onesweep_tile<BITS, BLOCK, ITEMS, WIN, MODE, WITH_VALUES, LB, true>(
             td, keys_in, vals_in, keys_out, vals_out, n, shift, gh, gn, shift_next, lb, epoch, err, stage, whist,
             nhist, ddelta, scan_tmp, tiles);
     else
-        onesweep_tile<BITS, BLOCK, ITEMS, WIN, FIRST, WITH_VALUES, LB, false>(
+        onesweep_tile<BITS, BLOCK, ITEMS, WIN, MODE, WITH_VALUES, LB, false>(
             td, keys_in, vals_in, keys_out, vals_out, n, shift, gh, gn, shift_next, lb, epoch, err, stage, whist,
             nhist, ddelta, scan_tmp, tiles);
 }
@@ -560,22 +673,23 @@ __global__ __launch_bounds__(BLOCK, (kMinBlocks<BLOCK, ITEMS>)) void onesweep_li
         const uint32_t* gh = ghist + static_cast<size_t>(t.w) * hist_stride;
         uint32_t* gn = ghist_next ? ghist_next + static_cast<size_t>(t.w) * hist_stride : nullptr;
         if (td.count == static_cast<uint32_t>(TILE))
-            onesweep_tile<BITS, BLOCK, ITEMS, WIN, false, true, LB, true>(
+            onesweep_tile<BITS, BLOCK, ITEMS, WIN, kLater, true, LB, true>(
                 td, keys_in, vals_in, keys_out, vals_out, n, shift, gh, gn, shift_next, lb, epoch, err, stage, whist,
                 nhist, ddelta, scan_tmp, tiles);
         else
-            onesweep_tile<BITS, BLOCK, ITEMS, WIN, false, true, LB, false>(
+            onesweep_tile<BITS, BLOCK, ITEMS, WIN, kLater, true, LB, false>(
                 td, keys_in, vals_in, keys_out, vals_out, n, shift, gh, gn, shift_next, lb, epoch, err, stage, whist,
                 nhist, ddelta, scan_tmp, tiles);
         __syncthreads();  // shared state and the slot are reused by the next tile
     }
 }
 
-// ---- prefix split: the top two digits, then every bucket on its own ---------
+// ---- prefix split: the top digits, then every bucket on its own ---------------
 //
 // For particle keys the three most significant digits (27 bits: the level-9
-// octant of a key) are sorted first, by onesweep passes. The keys then
-// form runs of one prefix ("buckets"), each still in input order. A block
+// octant of a key), or four where the keys crowd (see decide_depth), are sorted
+// first, by onesweep passes. The keys then form runs of one prefix
+// ("buckets"), each still in input order. A block
 // owns the buckets that start in its chunk of kLocalChunk keys and sorts each
 // segment of at most kLocalCap keys in LDS, by an LSD sort over only the bits
 // in which the segment's keys differ (stable, so input order is kept among
@@ -919,7 +1033,8 @@ __device__ __forceinline__ void list_large(const LargeList& L, uint32_t start, u
 template <int BITS, int BLOCK, int ITEMS, bool SEG>
 __global__ __launch_bounds__(BLOCK, kLocalBlocksPerCU * BLOCK / (4 * kWave)) void local_sort_kernel(
     uint64_t* keys, uint32_t* vals, uint32_t n, uint32_t pshift, LargeList large, uint32_t* err,
-    const uint32_t* seg_base, uint32_t n_sets, const uint32_t* chunk_set) {
+    const uint32_t* __restrict__ deep, uint32_t deep_shift, const uint32_t* seg_base, uint32_t n_sets, const uint32_t* chunk_set) {
+    if (!SEG && *deep) pshift = deep_shift;  // the buckets of the extra digit
     const uint64_t* kin = keys;
     const uint32_t* vin = vals;
     uint64_t* kout = keys;
@@ -1095,31 +1210,38 @@ struct PassArgs {
     uint32_t epoch;
     uint32_t* err;
     bool wide;  // 64-bit look-back words (n >= 2^30)
+    // a split sort's depth word, and what its extra pass wrote (see kEither)
+    const uint32_t* deep;
+    const uint64_t* deep_keys;
+    const uint32_t* deep_vals;
 };
 
-template <int BITS, int BLOCK, int ITEMS, int WIN, bool FIRST, bool VALS>
+template <int BITS, int BLOCK, int ITEMS, int WIN, int MODE, bool VALS>
 void launch_one(const PassArgs& a, hipStream_t stream) {
     constexpr uint32_t tile = BLOCK * ITEMS;
     const dim3 grid((a.n + tile - 1) / tile), block(BLOCK);
     if (a.wide)
-        hipLaunchKernelGGL((onesweep_kernel<BITS, BLOCK, ITEMS, WIN, FIRST, VALS, Lb64>), grid, block, 0, stream,
+        hipLaunchKernelGGL((onesweep_kernel<BITS, BLOCK, ITEMS, WIN, MODE, VALS, Lb64>), grid, block, 0, stream,
                            a.keys_in, a.vals_in, a.keys_out, a.vals_out, a.n, a.shift, a.ghist, a.ghist_next,
-                           a.shift_next, static_cast<uint64_t*>(a.lb), nullptr, a.epoch, a.err);
+                           a.shift_next, static_cast<uint64_t*>(a.lb), nullptr, a.epoch, a.err, a.deep, a.deep_keys,
+                           a.deep_vals);
     else
-        hipLaunchKernelGGL((onesweep_kernel<BITS, BLOCK, ITEMS, WIN, FIRST, VALS, Lb32>), grid, block, 0, stream,
+        hipLaunchKernelGGL((onesweep_kernel<BITS, BLOCK, ITEMS, WIN, MODE, VALS, Lb32>), grid, block, 0, stream,
                            a.keys_in, a.vals_in, a.keys_out, a.vals_out, a.n, a.shift, a.ghist, a.ghist_next,
                            a.shift_next, static_cast<uint32_t*>(a.lb), static_cast<uint32_t*>(a.lb_clear), a.epoch,
-                           a.err);
+                           a.err, a.deep, a.deep_keys, a.deep_vals);
 }
 
 template <int BITS, int BLOCK, int ITEMS, int WIN>
 void launch_pass_t(const PassArgs& a, bool first, bool with_values, hipStream_t stream) {
-    if (with_values && first)
-        launch_one<BITS, BLOCK, ITEMS, WIN, true, true>(a, stream);
+    if (with_values && a.deep_keys)
+        launch_one<BITS, BLOCK, ITEMS, WIN, kEither, true>(a, stream);
+    else if (with_values && first)
+        launch_one<BITS, BLOCK, ITEMS, WIN, kFirst, true>(a, stream);
     else if (with_values)
-        launch_one<BITS, BLOCK, ITEMS, WIN, false, true>(a, stream);
+        launch_one<BITS, BLOCK, ITEMS, WIN, kLater, true>(a, stream);
     else
-        launch_one<BITS, BLOCK, ITEMS, WIN, false, false>(a, stream);
+        launch_one<BITS, BLOCK, ITEMS, WIN, kLater, false>(a, stream);
 }
 
 struct SegArgs {
@@ -1130,16 +1252,16 @@ struct SegArgs {
     const uint32_t* live_tiles;  // NULL, or the device word holding how many tiles are in use
 };
 
-template <int BITS, int BLOCK, int ITEMS, int WIN, bool FIRST, bool VALS>
+template <int BITS, int BLOCK, int ITEMS, int WIN, int MODE, bool VALS>
 void launch_one_seg(const PassArgs& a, const SegArgs& g, hipStream_t stream) {
     const dim3 grid(g.n_tiles), block(BLOCK);
     if (a.wide)
-        hipLaunchKernelGGL((onesweep_seg_kernel<BITS, BLOCK, ITEMS, WIN, FIRST, VALS, Lb64>), grid, block, 0, stream,
+        hipLaunchKernelGGL((onesweep_seg_kernel<BITS, BLOCK, ITEMS, WIN, MODE, VALS, Lb64>), grid, block, 0, stream,
                            a.keys_in, a.vals_in, a.keys_out, a.vals_out, a.n, a.shift, a.ghist, a.ghist_next,
                            a.shift_next, g.hist_stride, g.tiles, g.seg_base, static_cast<uint64_t*>(a.lb), nullptr,
                            a.epoch, a.err, g.live_tiles);
     else
-        hipLaunchKernelGGL((onesweep_seg_kernel<BITS, BLOCK, ITEMS, WIN, FIRST, VALS, Lb32>), grid, block, 0, stream,
+        hipLaunchKernelGGL((onesweep_seg_kernel<BITS, BLOCK, ITEMS, WIN, MODE, VALS, Lb32>), grid, block, 0, stream,
                            a.keys_in, a.vals_in, a.keys_out, a.vals_out, a.n, a.shift, a.ghist, a.ghist_next,
                            a.shift_next, g.hist_stride, g.tiles, g.seg_base, static_cast<uint32_t*>(a.lb),
                            static_cast<uint32_t*>(a.lb_clear), a.epoch, a.err, g.live_tiles);
@@ -1148,11 +1270,11 @@ void launch_one_seg(const PassArgs& a, const SegArgs& g, hipStream_t stream) {
 template <int BITS, int BLOCK, int ITEMS, int WIN>
 void launch_seg_t(const PassArgs& a, const SegArgs& g, bool first, bool with_values, hipStream_t stream) {
     if (with_values && first)
-        launch_one_seg<BITS, BLOCK, ITEMS, WIN, true, true>(a, g, stream);
+        launch_one_seg<BITS, BLOCK, ITEMS, WIN, kFirst, true>(a, g, stream);
     else if (with_values)
-        launch_one_seg<BITS, BLOCK, ITEMS, WIN, false, true>(a, g, stream);
+        launch_one_seg<BITS, BLOCK, ITEMS, WIN, kLater, true>(a, g, stream);
     else
-        launch_one_seg<BITS, BLOCK, ITEMS, WIN, false, false>(a, g, stream);
+        launch_one_seg<BITS, BLOCK, ITEMS, WIN, kLater, false>(a, g, stream);
 }
 
 constexpr uint32_t kListGrid = 512;  // blocks of a pass over a device-written tile table
@@ -1201,13 +1323,16 @@ constexpr int kNumVariants = sizeof(kVariants) / sizeof(kVariants[0]);
 constexpr int kBuiltinVariant = 0;
 
 // Split sorts of particle keys: 9-bit digits, the top three first (the
-// level-9 octant), then four low passes for the listed buckets
-// (63 = 3 * 9 + 36 bits). The top passes end in the output arrays, where the
+// level-9 octant), before them the digit below if the keys crowd, then four low
+// passes for the listed buckets (63 = 3 * 9 + 36 bits; after the extra digit the
+// last of them finds one digit in a bucket). The top passes end in the output arrays, where the
 // buckets are sorted in place and the low passes end too.
 constexpr int kSplitBits = 9;
 constexpr int kSplitTop = 3;
 constexpr int kLowPasses = 4;
 constexpr uint32_t kSplitShift = 63 - kSplitTop * kSplitBits;  // the prefix is key >> 36
+constexpr uint32_t kDeepShift = kSplitShift - kSplitBits;      // ... or key >> 27, after the extra digit
+constexpr int kDeepWord = 16;                                  // its word among the bucket-list counters
 static_assert(kSplitTop % 2 == 1 && kLowPasses % 2 == 0, "top passes and low passes end in the output arrays");
 constexpr int kGhistWords = kMaxPasses * kMaxRadix + 64;      // digit counts, then the bucket-list counters
 
@@ -1221,6 +1346,7 @@ struct SortWs {
     size_t rows;  // look-back rows: tiles of the smallest tile size, plus the listed buckets' extra tiles
     // bucket list of a split sort (with_perm only)
     uint32_t* large_count;
+    uint32_t* deep;  // the depth word
     uint4* large_tiles;
     uint32_t* large_start;
     uint32_t* large_hist;
@@ -1238,6 +1364,7 @@ SortWs carve_sort(void* ws, size_t n, bool with_perm) {
     s.vals_alt = with_perm ? c.take<uint32_t>(n) : nullptr;
     s.ghist = c.take<uint32_t>(kGhistWords);
     s.large_count = s.ghist + kMaxPasses * kMaxRadix;
+    s.deep = s.large_count + kDeepWord;
     s.err = c.take<uint32_t>(1);
     // a listed bucket holds more than kLocalCap keys; its tiles number at most
     // its keys / tile + 1
@@ -1278,11 +1405,19 @@ int sort_passes(size_t n, int sig_bits, bool with_perm, int variant) {
     return (sig_bits + var.bits - 1) / var.bits;
 }
 
+namespace {
+// the second set of 32-bit look-back rows, which a split sort's extra pass uses
+uint64_t* second_rows(const SortWs& s, bool wide) {
+    return wide ? nullptr : reinterpret_cast<uint64_t*>(static_cast<uint32_t*>(s.lb) + s.rows * kMaxRadix);
+}
+}  // namespace
+
 cstone_status sort_prepare(void* ws, size_t n, bool with_perm, hipStream_t stream, uint32_t* clear_word,
                            int variant) {
     SortWs s = carve_sort(ws, n, with_perm);
-    // only the first pass's look-back rows need clearing: each pass clears the
-    // rows of the next (32-bit words), or words carry the pass's epoch (64-bit)
+    // only the first pass's look-back rows need clearing (a split sort's two
+    // first passes'): each pass clears the rows of the next (32-bit words), or
+    // words carry the pass's epoch (64-bit)
     const Variant& var = variant_or_builtin(variant);
     const size_t tile = static_cast<size_t>(var.block) * var.items;
     const size_t words = ((n + tile - 1) / tile) << var.bits;
@@ -1290,7 +1425,8 @@ cstone_status sort_prepare(void* ws, size_t n, bool with_perm, hipStream_t strea
     const size_t lb_words = std::min(s.lb_bytes / 8, wide ? words : (words + 1) / 2);
     const size_t init_grid = std::max<size_t>(4, std::min<size_t>((lb_words + 255) / 256, 1024));
     hipLaunchKernelGGL(sort_init_kernel, dim3(init_grid), dim3(256), 0, stream, s.ghist,
-                       static_cast<size_t>(kGhistWords), s.err, static_cast<uint64_t*>(s.lb), lb_words, clear_word);
+                       static_cast<size_t>(kGhistWords), s.err, static_cast<uint64_t*>(s.lb), second_rows(s, wide),
+                       lb_words, clear_word);
     CS_HIP(hipGetLastError());
     return CSTONE_OK;
 }
@@ -1300,15 +1436,15 @@ void sort_key_parts(void* ws, size_t n, bool with_perm, int sig_bits, int varian
     const Variant& var = variant_or_builtin(variant);
     const bool split = use_split(n, sig_bits, with_perm, var);
     *mask = (1u << var.bits) - 1u;
-    *shift = split ? kSplitShift : 0u;
-    *digits = split ? static_cast<uint32_t>(kSplitTop) : 1u;
+    *shift = split ? kDeepShift : 0u;
+    *digits = split ? static_cast<uint32_t>(kSplitTop) + 1u : 1u;
     const SortWs s = carve_sort(ws, n, with_perm);
     *hist_parts = s.key_parts;
     *bad_parts = s.key_bad;
 }
 
-cstone_status sort_setup_from_keys(void* ws, size_t n, bool with_perm, int variant, uint32_t parts, uint32_t* flag,
-                                   uint64_t* clear, size_t clear_words, hipStream_t stream) {
+cstone_status sort_setup_from_keys(void* ws, size_t n, bool with_perm, int variant, uint32_t parts, const uint64_t* keys,
+                                   uint32_t* flag, uint64_t* clear, size_t clear_words, hipStream_t stream) {
     if (!with_perm || parts == 0 || parts > kKeyBlocksMax) return CSTONE_ERR_INVALID_ARG;
     if (variant < 0 || variant >= kNumVariants) return CSTONE_ERR_INVALID_ARG;
     SortWs s = carve_sort(ws, n, with_perm);
@@ -1318,12 +1454,14 @@ cstone_status sort_setup_from_keys(void* ws, size_t n, bool with_perm, int varia
     const bool wide = n >= (1ull << 30);
     const size_t lb_words = std::min(s.lb_bytes / 8, wide ? words : (words + 1) / 2);
     const uint32_t radix = 1u << var.bits;
-    const uint32_t digits = use_split(n, 63, with_perm, var) ? static_cast<uint32_t>(kSplitTop) : 1u;
-    // the summing blocks and the flag block, and enough blocks besides for the clearing
-    const uint32_t grid = std::max<uint32_t>(digits * kMaxRadix / kSetupCols + 1, kMaxRadix + 1);
+    const bool split = use_split(n, 63, with_perm, var);
+    const uint32_t digits = split ? static_cast<uint32_t>(kSplitTop) + 1u : 1u;
+    // the summing blocks, the flag block and the depth block, and enough blocks besides for the clearing
+    const uint32_t grid = std::max<uint32_t>(digits * kMaxRadix / kSetupCols + 2, kMaxRadix + 1);
     hipLaunchKernelGGL(sort_setup_kernel, dim3(grid), dim3(kKeyBlocksMax), 0, stream, s.ghist,
-                       static_cast<size_t>(kGhistWords), s.err, static_cast<uint64_t*>(s.lb), lb_words, s.key_parts,
-                       parts, radix, digits, s.key_bad, flag, clear, clear_words);
+                       static_cast<size_t>(kGhistWords), s.err, static_cast<uint64_t*>(s.lb),
+                       split ? second_rows(s, wide) : nullptr, lb_words, s.key_parts, parts, radix, digits, s.key_bad,
+                       flag, clear, clear_words, keys, static_cast<uint32_t>(n), split ? s.deep : nullptr);
     CS_HIP(hipGetLastError());
     return CSTONE_OK;
 }
@@ -1341,6 +1479,21 @@ cstone_status launch_split(const uint64_t* keys_in, uint64_t* keys_out, uint32_t
     if (pass_events) CS_HIP(hipEventRecord(pass_events[0], stream));
     const uint64_t* src_k = keys_in;
     const uint32_t* src_v = nullptr;
+    {  // the extra pass, left out on the device unless the depth word is set: keys_in -> alt
+        PassArgs a{};
+        a.keys_in = keys_in;
+        a.keys_out = s.keys_alt;
+        a.vals_out = s.vals_alt;
+        a.n = static_cast<uint32_t>(n);
+        a.shift = kDeepShift;
+        a.ghist = s.ghist;
+        a.wide = wide;
+        a.lb = wide ? s.lb : static_cast<void*>(lb32[1]);
+        a.epoch = kMaxPasses + 1;
+        a.err = err;
+        a.deep = s.deep;
+        if (n >= kDeepMinKeys) var.launch(a, true, true, stream);
+    }
     for (int p = 0; p < kSplitTop; ++p) {
         const bool to_out = ((kSplitTop - 1 - p) % 2) == 0;
         PassArgs a{};
@@ -1350,10 +1503,15 @@ cstone_status launch_split(const uint64_t* keys_in, uint64_t* keys_out, uint32_t
         a.vals_out = to_out ? perm_out : s.vals_alt;
         a.n = static_cast<uint32_t>(n);
         a.shift = kSplitShift + p * kSplitBits;
-        a.ghist = s.ghist + p * radix;
+        a.ghist = s.ghist + (p + 1) * radix;
         // every top digit's counts came from the key kernel (top_counted), else
         // each top pass counts the next one's
-        a.ghist_next = p + 1 < kSplitTop && !top_counted ? s.ghist + (p + 1) * radix : nullptr;
+        a.ghist_next = p + 1 < kSplitTop && !top_counted ? s.ghist + (p + 2) * radix : nullptr;
+        if (p == 0 && n >= kDeepMinKeys) {
+            a.deep = s.deep;
+            a.deep_keys = s.keys_alt;
+            a.deep_vals = s.vals_alt;
+        }
         a.shift_next = kSplitShift + (p + 1) * kSplitBits;
         a.wide = wide;
         a.lb = wide ? s.lb : static_cast<void*>(lb32[p & 1]);
@@ -1384,7 +1542,7 @@ cstone_status launch_split(const uint64_t* keys_in, uint64_t* keys_out, uint32_t
     const uint32_t chunks = static_cast<uint32_t>((n + kLocalChunk - 1) / kLocalChunk);
     hipLaunchKernelGGL((local_sort_kernel<kSplitBits, kLocalBlock, kLocalItems, false>), dim3(chunks),
                        dim3(kLocalBlock), 0, stream, keys_out, perm_out, static_cast<uint32_t>(n), kSplitShift, L, err,
-                       static_cast<const uint32_t*>(nullptr), 0u, static_cast<const uint32_t*>(nullptr));
+                       s.deep, kDeepShift, static_cast<const uint32_t*>(nullptr), 0u, static_cast<const uint32_t*>(nullptr));
     if (pass_events) CS_HIP(hipEventRecord(pass_events[3], stream));
     if (s.max_buckets > 0) {  // some bucket may be longer than one block sorts
         hipLaunchKernelGGL(large_hist_kernel, dim3(std::min(L.max_tiles, kListGrid)), dim3(512), 0, stream, keys_out,
@@ -1440,9 +1598,9 @@ cstone_status launch_sort(const uint64_t* keys_in, uint64_t* keys_out, uint32_t*
         if (st != CSTONE_OK) return st;
         const size_t hblocks =
             std::max<size_t>(1, std::min<size_t>((n + kHistBlock * 16 - 1) / (kHistBlock * 16), 1024));
-        hipLaunchKernelGGL(sort_hist0_kernel, dim3(hblocks), dim3(kHistBlock), 0, stream, keys_in,
-                           static_cast<uint32_t>(n), split ? kSplitShift : 0u, static_cast<uint32_t>(radix - 1),
-                           s.ghist);
+        hipLaunchKernelGGL(sort_hist0_kernel, dim3(split ? hblocks + 1 : hblocks), dim3(kHistBlock), 0, stream, keys_in,
+                           static_cast<uint32_t>(n), split ? kDeepShift : 0u, static_cast<uint32_t>(radix - 1),
+                           static_cast<uint32_t>(var.bits), s.ghist, split ? s.deep : nullptr);
     }
     uint32_t* err = err_word ? err_word : s.err;
     if (split)
@@ -1585,7 +1743,8 @@ cstone_status sort_seg_prepare(void* ws, size_t n_total, size_t n_tiles, uint32_
     const size_t init_grid =
         std::max<size_t>(4, std::min<size_t>((std::max(lb_words, gwords) + 255) / 256, 2048));
     hipLaunchKernelGGL(sort_init_kernel, dim3(init_grid), dim3(256), 0, stream, s.ghist, gwords, s.err,
-                       static_cast<uint64_t*>(s.lb), lb_words, static_cast<uint32_t*>(nullptr));
+                       static_cast<uint64_t*>(s.lb), static_cast<uint64_t*>(nullptr), lb_words,
+                       static_cast<uint32_t*>(nullptr));
     CS_HIP(hipGetLastError());
     return CSTONE_OK;
 }
@@ -1651,7 +1810,7 @@ cstone_status launch_split_seg(const uint64_t* keys_in, uint64_t* keys_out, uint
     L.wide = wide ? 1u : 0u;
     hipLaunchKernelGGL((local_sort_kernel<kSplitBits, kLocalBlock, kLocalItems, true>), dim3(chunks),
                        dim3(kLocalBlock), 0, stream, keys_out, perm_out, static_cast<uint32_t>(n_total), kSplitShift,
-                       L, err, seg_base, n_sets,
+                       L, err, static_cast<const uint32_t*>(nullptr), kSplitShift, seg_base, n_sets,
                        static_cast<const uint32_t*>(s.chunk_set));
     if (s.max_buckets > 0) {  // some bucket may be longer than one block sorts
         hipLaunchKernelGGL(large_hist_kernel, dim3(std::min(L.max_tiles, kListGrid)), dim3(512), 0, stream, keys_out,
