@@ -19,6 +19,8 @@ bool box_ok(const cstone_box* b) {
 
 constexpr size_t kMaxN = 0xffffffffull;  // counts, perm, CO and LO are uint32
 
+constexpr size_t kListMaxKeys = size_t{1} << 25;
+
 size_t nodes_of(size_t nl) { return nl + (nl ? (nl - 1) / 7 : 0); }
 
 __global__ void clear_word_kernel(uint32_t* w) { *w = 0; }
@@ -228,9 +230,18 @@ cstone_status cstone_build(const double* x, const double* y, const double* z, si
             hipLaunchKernelGGL(clear_word_kernel, dim3(1), dim3(1), 0, stream, flag);
             if (mark(1) != hipSuccess) { s = CSTONE_ERR_DEVICE; break; }
         }
+        // The sort's low passes (five launches) rarely find a bucket to sort.
+        // Where the host looks at the build's end anyway, they are only run if
+        // it then sees one listed, and the tree once more; from kListMaxKeys on,
+        // where the launches no longer show, and where the tree's workspace
+        // would overwrite the list, they are always enqueued.
+        const uint32_t* listed = nullptr;
+        if (n && n < kListMaxKeys && tree_possible(n, max_iters) &&
+            tree_workspace_bytes(n, n_crit, leaf_capacity, nl > 1) <= sort_scratch_bytes(n))
+            listed = sort_listed_word(stage_ws, n, variant);
         // the sort reports a failed device-side wait into the same flag word
         s = launch_sort(keys, sorted_keys, perm, n, 63, stage_ws, stage_bytes, stream,
-                        timed && n ? pass_ev : nullptr, /*prepared=*/true, variant, flag);
+                        timed && n ? pass_ev : nullptr, /*prepared=*/true, variant, flag, /*low_passes=*/!listed);
         if (s != CSTONE_OK) break;
         if (mark(2) != hipSuccess) { s = CSTONE_ERR_DEVICE; break; }
         if (nl == 0) nl = 1;  // start from the root leaf {0, 8^L}
@@ -238,9 +249,18 @@ cstone_status cstone_build(const double* x, const double* y, const double* z, si
         if (tree_possible(n, max_iters)) {  // tree and links are enqueued together, and the host looks once
             TreePass tree;
             if (tree.run(sorted_keys, n, n_crit, leaves, nl, leaf_capacity, counts, node_keys, child, level_offsets,
-                         stage_ws, stage_bytes, tree_state, flag, stream)) {
+                         stage_ws, stage_bytes, tree_state, flag, listed, stream)) {
                 if (mark(3) != hipSuccess || mark(4) != hipSuccess) { s = CSTONE_ERR_DEVICE; break; }
                 if ((s = tree.wait(&done)) != CSTONE_OK) break;
+                if (tree.listed) {  // some buckets are not sorted yet: sort them, and the tree again
+                    s = launch_sort_low(sorted_keys, perm, n, stage_ws, variant, flag, stream);
+                    if (s != CSTONE_OK) break;
+                    if (mark(2) != hipSuccess) { s = CSTONE_ERR_DEVICE; break; }
+                    tree.run(sorted_keys, n, n_crit, leaves, nl, leaf_capacity, counts, node_keys, child, level_offsets,
+                             stage_ws, stage_bytes, nullptr, flag, nullptr, stream);
+                    if (mark(3) != hipSuccess || mark(4) != hipSuccess) { s = CSTONE_ERR_DEVICE; break; }
+                    if ((s = tree.wait(&done)) != CSTONE_OK) break;
+                }
                 if (done) {
                     *n_leaves = tree.n_leaves;
                     if (iters_done) *iters_done = tree.rounds;

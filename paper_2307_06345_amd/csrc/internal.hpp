@@ -42,7 +42,16 @@ size_t sort_workspace_bytes(size_t n, bool with_perm);
 cstone_status launch_sort(const uint64_t* keys_in, uint64_t* keys_out, uint32_t* perm_out, size_t n,
                           int sig_bits, void* ws, size_t ws_bytes, hipStream_t stream,
                           hipEvent_t* pass_events = nullptr, bool prepared = false, int variant = -1,
-                          uint32_t* err_word = nullptr);
+                          uint32_t* err_word = nullptr, bool low_passes = true);
+// A sort enqueued without its low passes (a split sort of particle keys) is
+// complete unless *sort_listed_word (buckets listed for them; NULL if there are
+// none by the sizes) ends up non-zero; launch_sort_low then runs them, with the
+// same workspace, of which the first sort_scratch_bytes may have been used for
+// something else in between.
+const uint32_t* sort_listed_word(void* ws, size_t n, int variant);
+size_t sort_scratch_bytes(size_t n);
+cstone_status launch_sort_low(uint64_t* keys_out, uint32_t* perm_out, size_t n, void* ws, int variant,
+                              uint32_t* err_word, hipStream_t stream);
 // clear_word: NULL, or one caller word zeroed by the same launch; variant: the
 // sort shape the passes will use
 cstone_status sort_prepare(void* ws, size_t n, bool with_perm, hipStream_t stream, uint32_t* clear_word,
@@ -182,11 +191,14 @@ struct TreeState {
     uint64_t inter;        // from another array: bound on the leaves of every round
     uint32_t max_diff;     // from another array: largest level difference of overlapping leaves
     uint32_t depth;        // level of the deepest leaf
+    uint32_t listed;       // buckets that the sort left for its low passes: the tree is of unsorted keys
+    uint32_t unused;
 };
+static_assert(sizeof(TreeState) % 8 == 0, "cleared by words");
 
 size_t tree_tiles(size_t n);
 size_t tree_slots(size_t n, uint32_t n_crit, size_t cap);  // of the list of internal nodes
-size_t tree_workspace_bytes(size_t n, uint32_t n_crit, size_t cap);
+size_t tree_workspace_bytes(size_t n, uint32_t n_crit, size_t cap, bool incremental = true);
 // whether the tree can stand for the rounds: they run to convergence (max_iters
 // 0 or at least L + 1) and there are particles
 bool tree_possible(size_t n, uint32_t max_iters);
@@ -200,7 +212,9 @@ public:
     // False (nothing enqueued) if ws is too short.
     bool run(const uint64_t* sorted_keys, size_t n, uint32_t n_crit, uint64_t* leaves, size_t nl0, size_t cap,
              uint32_t* counts, uint64_t* node_keys, uint32_t* child, uint32_t* level_offsets, void* ws, size_t ws_bytes,
-             TreeState* cleared, const uint32_t* input_flags, hipStream_t stream);
+             TreeState* cleared, const uint32_t* input_flags, const uint32_t* listed, hipStream_t stream);
+    // listed: NULL, or the word that says whether the keys' sort is incomplete
+    // (see sort_listed_word); `leaves` is then left alone unless from the root.
     // Synchronises. *fits false: the tree or a round on the way to it exceeds
     // the capacity; `leaves` holds the start array unless that was the root,
     // and the rounds have to say how far they come.
@@ -208,6 +222,7 @@ public:
     size_t n_leaves = 0;
     uint32_t rounds = 0;
     uint32_t input_flags = 0;
+    uint32_t listed = 0;
 
 private:
     bool incremental_ = false;

@@ -595,7 +595,7 @@ cstone_status run_rebalance(const uint64_t* P, size_t n, uint32_t n_crit, uint64
     if (tree_possible(n, max_iters)) {
         TreePass tree;
         if (tree.run(P, n, n_crit, leaves, *n_leaves, cap, counts, nullptr, nullptr, nullptr, ws, ws_bytes, nullptr,
-                     nullptr, stream)) {
+                     nullptr, nullptr, stream)) {
             bool fits = false;
             if ((s = tree.wait(&fits)) != CSTONE_OK) return s;
             if (fits) {

@@ -61,21 +61,29 @@ constexpr uint32_t kDeepBucket = 16;
 constexpr uint32_t kDeepPairs = 4;  // fewer pairs in the sample may be chance
 constexpr uint32_t kDeepMinKeys = 1u << 20;  // shorter sorts gain less than the extra launch costs where it is left out
 
-// All threads of the block (blockDim.x divides kDeepSample); slots, pairs: LDS.
+// All THREADS threads of the block; slots, pairs: LDS.
+template <uint32_t THREADS>
 __device__ __forceinline__ void decide_depth(const uint64_t* __restrict__ keys, uint32_t n, uint32_t* slots,
                                              uint32_t* pairs, uint32_t* deep) {
-    for (uint32_t i = threadIdx.x; i < kDeepSlots; i += blockDim.x) slots[i] = 0;
+    constexpr uint32_t kEach = kDeepSample / THREADS;
+    // one place in each of kDeepSample equal shares of the keys, scattered
+    // within it by a multiplicative hash of the share's number; all in flight
+    uint64_t key[kEach];
+#pragma unroll
+    for (uint32_t q = 0; q < kEach; ++q) {
+        const uint32_t i = q * THREADS + threadIdx.x;
+        const uint64_t a = static_cast<uint64_t>(n) * i / kDeepSample;
+        const uint64_t len = static_cast<uint64_t>(n) * (i + 1) / kDeepSample - a;
+        key[q] = keys[a + ((static_cast<uint64_t>(i * 2654435761u) * len) >> 32)];
+    }
+    for (uint32_t i = threadIdx.x; i < kDeepSlots; i += THREADS) slots[i] = 0;
     if (threadIdx.x == 0) *pairs = 0;
     __syncthreads();
     uint32_t mine = 0;
-    for (uint32_t i = threadIdx.x; i < kDeepSample; i += blockDim.x) {
-        // one place in each of kDeepSample equal shares of the keys, scattered
-        // within it by a multiplicative hash of the share's number
-        const uint64_t a = static_cast<uint64_t>(n) * i / kDeepSample;
-        const uint64_t len = static_cast<uint64_t>(n) * (i + 1) / kDeepSample - a;
-        const uint64_t at = a + ((static_cast<uint64_t>(i * 2654435761u) * len) >> 32);
+#pragma unroll
+    for (uint32_t q = 0; q < kEach; ++q) {
         // word: prefix + 1 (0 is free) << 4, and the keys seen with it, counted up to 15
-        const uint32_t tag = (static_cast<uint32_t>(keys[at] >> 36) + 1u) << 4;
+        const uint32_t tag = (static_cast<uint32_t>(key[q] >> 36) + 1u) << 4;
         for (uint32_t s = (tag * 2654435761u) >> 20;; s = (s + 1) & (kDeepSlots - 1)) {  // the table is half empty
             const uint32_t old = atomicCAS(&slots[s], 0u, tag | 1u);
             if (old == 0) break;
@@ -161,7 +169,7 @@ __global__ __launch_bounds__(kKeyBlocksMax) void sort_setup_kernel(uint32_t* ghi
         }
     } else if (j == sums + 1 && deep) {  // block-uniform: the split's depth
         if (n >= kDeepMinKeys)
-            decide_depth(keys, n, red, &pairs, deep);
+            decide_depth<kKeyBlocksMax>(keys, n, red, &pairs, deep);
         else if (tid == 0)
             *deep = 0;
     }
@@ -180,7 +188,7 @@ __global__ __launch_bounds__(kHistBlock) void sort_hist0_kernel(const uint64_t* 
     const uint32_t blocks = deep ? gridDim.x - 1 : gridDim.x;
     if (blockIdx.x == blocks) {  // block-uniform
         if (n >= kDeepMinKeys)
-            decide_depth(keys, n, h, &pairs, deep);
+            decide_depth<kHistBlock>(keys, n, h, &pairs, deep);
         return;  // (the word is cleared)
     }
     const uint32_t words = deep ? 2 * kMaxRadix : kMaxRadix;
@@ -1468,12 +1476,61 @@ cstone_status sort_setup_from_keys(void* ws, size_t n, bool with_perm, int varia
 
 namespace {
 
+LargeList large_list(const SortWs& s, size_t n, const Variant& var, bool wide) {
+    const uint32_t tile = static_cast<uint32_t>(var.block * var.items);
+    LargeList L{};
+    L.count = s.large_count;
+    L.tiles = s.large_tiles;
+    L.start = s.large_start;
+    L.hist = s.large_hist;
+    L.lb = s.lb;
+    L.stride = kLowPasses * kMaxRadix;
+    L.row_words = kMaxRadix;
+    L.tile = tile;
+    L.max_buckets = static_cast<uint32_t>(s.max_buckets);
+    L.max_tiles = static_cast<uint32_t>((n + tile - 1) / tile + s.max_buckets);
+    L.wide = wide ? 1u : 0u;
+    return L;
+}
+
+// The low passes over the buckets that the bucket kernel listed.
+void launch_low(uint64_t* keys_out, uint32_t* perm_out, size_t n, const SortWs& s, const Variant& var, bool wide,
+                hipStream_t stream, uint32_t* err) {
+    constexpr int radix = 1 << kSplitBits;
+    uint32_t* lb32[2] = {static_cast<uint32_t*>(s.lb), static_cast<uint32_t*>(s.lb) + s.rows * kMaxRadix};
+    const LargeList L = large_list(s, n, var, wide);
+    if (s.max_buckets > 0) {  // some bucket may be longer than one block sorts
+        hipLaunchKernelGGL(large_hist_kernel, dim3(std::min(L.max_tiles, kListGrid)), dim3(512), 0, stream, keys_out,
+                           static_cast<uint32_t>(n), L, static_cast<uint32_t>(radix - 1));
+        SegArgs g{s.large_tiles, s.large_start, L.max_tiles, L.stride, s.large_count + 1};
+        for (int p = 0; p < kLowPasses; ++p) {
+            const bool from_alt = (p % 2) == 1;
+            PassArgs a{};
+            a.keys_in = from_alt ? s.keys_alt : keys_out;
+            a.vals_in = from_alt ? s.vals_alt : perm_out;
+            a.keys_out = from_alt ? keys_out : s.keys_alt;
+            a.vals_out = from_alt ? perm_out : s.vals_alt;
+            a.n = static_cast<uint32_t>(n);
+            a.shift = static_cast<uint32_t>(p * kSplitBits);
+            a.ghist = s.large_hist + p * radix;
+            a.ghist_next = p + 1 < kLowPasses ? s.large_hist + (p + 1) * radix : nullptr;
+            a.shift_next = static_cast<uint32_t>((p + 1) * kSplitBits);
+            a.wide = wide;
+            a.lb = wide ? s.lb : static_cast<void*>(lb32[p & 1]);
+            a.lb_clear = (!wide && p + 1 < kLowPasses) ? static_cast<void*>(lb32[(p + 1) & 1]) : nullptr;
+            a.epoch = static_cast<uint32_t>(kSplitTop + 1 + p);
+            a.err = err;
+            var.launch_list(a, g, s.large_count + 2 + p, stream);  // a tile counter per pass, cleared at set-up
+        }
+    }
+}
+
 // Split sort (see the prefix-split kernels): top passes keys_in -> keys_out ->
 // alt -> keys_out, buckets sorted in place in keys_out, low passes over the
 // listed buckets keys_out -> alt -> ... -> keys_out.
 cstone_status launch_split(const uint64_t* keys_in, uint64_t* keys_out, uint32_t* perm_out, size_t n,
                            const SortWs& s, const Variant& var, bool wide, hipStream_t stream,
-                           hipEvent_t* pass_events, uint32_t* err, bool top_counted) {
+                           hipEvent_t* pass_events, uint32_t* err, bool top_counted, bool low_passes) {
     constexpr int radix = 1 << kSplitBits;
     uint32_t* lb32[2] = {static_cast<uint32_t*>(s.lb), static_cast<uint32_t*>(s.lb) + s.rows * kMaxRadix};
     if (pass_events) CS_HIP(hipEventRecord(pass_events[0], stream));
@@ -1526,48 +1583,13 @@ cstone_status launch_split(const uint64_t* keys_in, uint64_t* keys_out, uint32_t
         if (pass_events && (p == 0 || p == kSplitTop - 1))
             CS_HIP(hipEventRecord(pass_events[p == 0 ? 1 : 2], stream));
     }
-    const uint32_t tile = static_cast<uint32_t>(var.block * var.items);
-    LargeList L{};
-    L.count = s.large_count;
-    L.tiles = s.large_tiles;
-    L.start = s.large_start;
-    L.hist = s.large_hist;
-    L.lb = wide ? s.lb : static_cast<void*>(lb32[0]);
-    L.stride = kLowPasses * kMaxRadix;
-    L.row_words = kMaxRadix;
-    L.tile = tile;
-    L.max_buckets = static_cast<uint32_t>(s.max_buckets);
-    L.max_tiles = static_cast<uint32_t>((n + tile - 1) / tile + s.max_buckets);
-    L.wide = wide ? 1u : 0u;
+    const LargeList L = large_list(s, n, var, wide);
     const uint32_t chunks = static_cast<uint32_t>((n + kLocalChunk - 1) / kLocalChunk);
     hipLaunchKernelGGL((local_sort_kernel<kSplitBits, kLocalBlock, kLocalItems, false>), dim3(chunks),
                        dim3(kLocalBlock), 0, stream, keys_out, perm_out, static_cast<uint32_t>(n), kSplitShift, L, err,
                        s.deep, kDeepShift, static_cast<const uint32_t*>(nullptr), 0u, static_cast<const uint32_t*>(nullptr));
     if (pass_events) CS_HIP(hipEventRecord(pass_events[3], stream));
-    if (s.max_buckets > 0) {  // some bucket may be longer than one block sorts
-        hipLaunchKernelGGL(large_hist_kernel, dim3(std::min(L.max_tiles, kListGrid)), dim3(512), 0, stream, keys_out,
-                           static_cast<uint32_t>(n), L, static_cast<uint32_t>(radix - 1));
-        SegArgs g{s.large_tiles, s.large_start, L.max_tiles, L.stride, s.large_count + 1};
-        for (int p = 0; p < kLowPasses; ++p) {
-            const bool from_alt = (p % 2) == 1;
-            PassArgs a{};
-            a.keys_in = from_alt ? s.keys_alt : keys_out;
-            a.vals_in = from_alt ? s.vals_alt : perm_out;
-            a.keys_out = from_alt ? keys_out : s.keys_alt;
-            a.vals_out = from_alt ? perm_out : s.vals_alt;
-            a.n = static_cast<uint32_t>(n);
-            a.shift = static_cast<uint32_t>(p * kSplitBits);
-            a.ghist = s.large_hist + p * radix;
-            a.ghist_next = p + 1 < kLowPasses ? s.large_hist + (p + 1) * radix : nullptr;
-            a.shift_next = static_cast<uint32_t>((p + 1) * kSplitBits);
-            a.wide = wide;
-            a.lb = wide ? s.lb : static_cast<void*>(lb32[p & 1]);
-            a.lb_clear = (!wide && p + 1 < kLowPasses) ? static_cast<void*>(lb32[(p + 1) & 1]) : nullptr;
-            a.epoch = static_cast<uint32_t>(kSplitTop + 1 + p);
-            a.err = err;
-            var.launch_list(a, g, s.large_count + 2 + p, stream);  // a tile counter per pass, cleared at set-up
-        }
-    }
+    if (low_passes) launch_low(keys_out, perm_out, n, s, var, wide, stream, err);
     if (pass_events) CS_HIP(hipEventRecord(pass_events[4], stream));
     CS_HIP(hipGetLastError());
     return CSTONE_OK;
@@ -1577,7 +1599,7 @@ cstone_status launch_split(const uint64_t* keys_in, uint64_t* keys_out, uint32_t
 
 cstone_status launch_sort(const uint64_t* keys_in, uint64_t* keys_out, uint32_t* perm_out, size_t n,
                           int sig_bits, void* ws, size_t ws_bytes, hipStream_t stream, hipEvent_t* pass_events,
-                          bool prepared, int variant, uint32_t* err_word) {
+                          bool prepared, int variant, uint32_t* err_word, bool low_passes) {
     const bool with_perm = perm_out != nullptr;
     SortWs s = carve_sort(ws, n, with_perm);
     if (ws_bytes < s.bytes) return CSTONE_ERR_INVALID_ARG;
@@ -1604,7 +1626,8 @@ cstone_status launch_sort(const uint64_t* keys_in, uint64_t* keys_out, uint32_t*
     }
     uint32_t* err = err_word ? err_word : s.err;
     if (split)
-        return launch_split(keys_in, keys_out, perm_out, n, s, var, wide, stream, pass_events, err, prepared);
+        return launch_split(keys_in, keys_out, perm_out, n, s, var, wide, stream, pass_events, err, prepared,
+                            low_passes);
 
     uint32_t* lb32[2] = {static_cast<uint32_t*>(s.lb), static_cast<uint32_t*>(s.lb) + s.rows * kMaxRadix};
     if (pass_events) CS_HIP(hipEventRecord(pass_events[0], stream));
@@ -1636,6 +1659,26 @@ cstone_status launch_sort(const uint64_t* keys_in, uint64_t* keys_out, uint32_t*
     return CSTONE_OK;
 }
 
+const uint32_t* sort_listed_word(void* ws, size_t n, int variant) {
+    if (!use_split(n, 63, true, variant_or_builtin(variant))) return nullptr;
+    const SortWs s = carve_sort(ws, n, true);
+    return s.max_buckets ? s.large_count : nullptr;
+}
+
+size_t sort_scratch_bytes(size_t n) {  // keys_alt and vals_alt
+    Carve c(nullptr);
+    c.take<uint64_t>(n);
+    c.take<uint32_t>(n);
+    return c.off;
+}
+
+cstone_status launch_sort_low(uint64_t* keys_out, uint32_t* perm_out, size_t n, void* ws, int variant,
+                              uint32_t* err_word, hipStream_t stream) {
+    launch_low(keys_out, perm_out, n, carve_sort(ws, n, true), variant_or_builtin(variant), n >= (1ull << 30), stream,
+               err_word);
+    CS_HIP(hipGetLastError());
+    return CSTONE_OK;
+}
 
 // ---- segmented sort ---------------------------------------------------------
 

@@ -391,7 +391,8 @@ __global__ __launch_bounds__(kWriteBlock) void tree_write_kernel(const uint64_t*
                                                                  uint64_t* __restrict__ K, uint32_t* __restrict__ counts,
                                                                  uint64_t* __restrict__ nk, uint32_t* __restrict__ co,
                                                                  uint32_t* __restrict__ lo_out, TreeState* st,
-                                                                 const uint32_t* input_flags, TreeResults res) {
+                                                                 const uint32_t* input_flags, const uint32_t* listed,
+                                                                 TreeResults res) {
     __shared__ uint32_t before[kTreeRows], after[kTreeRows], totals[kTreeRows];
     __shared__ uint32_t found[kWriteWaves][kWave];  // per wave and group: particles that start children
     __shared__ uint64_t first_key[kWriteWaves][kWave];  // per wave: the chunk's nodes' first keys and particles
@@ -471,6 +472,7 @@ __global__ __launch_bounds__(kWriteBlock) void tree_write_kernel(const uint64_t*
                 st->n_leaves = nl;
                 st->depth = depth;
                 st->input_flags = input_flags ? *input_flags : 0u;
+                st->listed = listed ? *listed : 0u;
             }
         }
         if (fits) {
@@ -837,6 +839,7 @@ __global__ __launch_bounds__(kCmpBlock) void tree_compare_kernel(const uint64_t*
 __global__ __launch_bounds__(256) void tree_commit_kernel(const uint64_t* __restrict__ K, uint64_t* __restrict__ leaves,
                                                           uint64_t cap, TreeState* st) {
     const uint64_t nl = st->n_leaves;
+    if (st->listed) return;
     const bool fits = nl <= cap && st->inter <= cap;
     const size_t t = static_cast<size_t>(blockIdx.x) * 256 + threadIdx.x;
     if (!fits) {
@@ -876,8 +879,8 @@ __global__ void tree_clear_kernel(TreeState* st) { *st = TreeState{}; }
 
 }  // namespace
 
-size_t tree_workspace_bytes(size_t n, uint32_t n_crit, size_t cap) {
-    return carve_tree(nullptr, n, n_crit, cap, true).bytes;
+size_t tree_workspace_bytes(size_t n, uint32_t n_crit, size_t cap, bool incremental) {
+    return carve_tree(nullptr, n, n_crit, cap, incremental).bytes;
 }
 
 size_t tree_tiles(size_t n) { return tree_tiles_of(n); }
@@ -890,7 +893,8 @@ bool tree_possible(size_t n, uint32_t max_iters) {
 
 bool TreePass::run(const uint64_t* P, size_t n, uint32_t n_crit, uint64_t* leaves, size_t nl0, size_t cap,
                    uint32_t* counts, uint64_t* node_keys, uint32_t* child, uint32_t* level_offsets, void* ws,
-                   size_t ws_bytes, TreeState* cleared, const uint32_t* input_flags, hipStream_t stream) {
+                   size_t ws_bytes, TreeState* cleared, const uint32_t* input_flags, const uint32_t* listed,
+                   hipStream_t stream) {
     incremental_ = nl0 > 1;
     const TreeWs w = carve_tree(ws, n, n_crit, cap, incremental_);
     if (ws_bytes < w.bytes || cap >= 0xffffffffull) return false;
@@ -911,7 +915,7 @@ bool TreePass::run(const uint64_t* P, size_t n, uint32_t n_crit, uint64_t* leave
                            w.totals);
     hipLaunchKernelGGL(tree_write_kernel<false>, dim3(tiles), dim3(kWriteBlock), 0, stream, P, one, no_sets, no_table,
                        tiles, max_level, w.inodes, w.ipos, w.tile_off, w.below, w.rows, scanned, w.totals, K, counts,
-                       node_keys, child, level_offsets, st_, input_flags, TreeResults{});
+                       node_keys, child, level_offsets, st_, input_flags, listed, TreeResults{});
     if (incremental_) {
         const uint32_t grid = static_cast<uint32_t>(std::min<size_t>((cap + kCmpTile - 1) / kCmpTile, 1024));
         hipLaunchKernelGGL(tree_compare_kernel, dim3(grid), dim3(kCmpBlock), 0, stream, leaves,
@@ -929,6 +933,7 @@ cstone_status TreePass::wait(bool* fits) {
     CS_HIP(hipMemcpyAsync(&host, st_, sizeof host, hipMemcpyDeviceToHost, stream_));
     CS_HIP(hipStreamSynchronize(stream_));
     input_flags = host.input_flags;
+    listed = host.listed;
     n_leaves = host.nl;
     rounds = 1 + (incremental_ ? host.max_diff : host.depth);
     *fits = host.nl != 0;
@@ -988,7 +993,7 @@ cstone_status launch_batch_tree(const uint64_t* P, size_t n_total, const BatchSe
         hipLaunchKernelGGL(tree_write_kernel<true>, dim3(tiles), dim3(kWriteBlock), 0, stream, P, one, sets, tile_set,
                            tiles, max_level, w.inodes, w.ipos, w.tile_off, w.below, w.rows, scanned, w.totals, leaves,
                            counts, node_keys, child, level_offsets, static_cast<TreeState*>(nullptr),
-                           static_cast<const uint32_t*>(nullptr), res);
+                           static_cast<const uint32_t*>(nullptr), static_cast<const uint32_t*>(nullptr), res);
     }
     if (empty_sets)
         hipLaunchKernelGGL(tree_empty_sets_kernel, dim3((n_sets + 63) / 64), dim3(64), 0, stream, sets, n_sets, leaves,

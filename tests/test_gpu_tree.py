@@ -112,3 +112,27 @@ def test_rebalance_from_another_tree_at_tight_capacities(coarse, fine):
             last = [K0] + hist
             at = next(i for i, h in enumerate(last) if h.size - 1 > cap) - 1
             eq(e.value.buffer[: last[at].size], last[at], "last array that fitted")
+
+
+@pytest.mark.parametrize("n", [50001, (1 << 20) + 3])
+def test_rebuild_of_heaps_from_the_tree_before(n):
+    """Particles heaped on a few points: buckets that the sort leaves to its
+    low passes, which the build runs (with the tree) once it has seen them. The
+    tree before must still be there to start from."""
+    H, c = wl.HILBERT, 16
+    print("[case] rebuild of heaps", n, flush=True)
+    b = cs.Builder(n, c, leaf_capacity=n + 64)
+    first = points("uniform", n, 1)
+    b.build(*(cs.from_numpy(a, "cuda") for a in first), wl.UNIT_BOX, H, c)
+    K0 = oracle.build_leaves(np.sort(oracle.compute_keys(*first, wl.UNIT_BOX, H)[0]), c)
+    x, y, z = points("heaps", n, 2)
+    ref = oracle.build_tree(x, y, z, wl.UNIT_BOX, H, c)
+    _, _, rounds, _, _ = oracle.rebalance_iterate(ref["P"], K0, c)
+    for timed in (False, True):
+        b.n_leaves = K0.size - 1
+        b.leaves[: K0.size].copy_(cs.from_numpy(K0, "cuda"))
+        r = b.build(*(cs.from_numpy(a, "cuda") for a in (x, y, z)), wl.UNIT_BOX, H, c, incremental=True, timed=timed)
+        for name, got in (("P", r.sorted_keys), ("perm", r.perm), ("K", r.leaves), ("counts", r.counts),
+                          ("NK", r.node_keys), ("CO", r.child), ("LO", r.level_offsets)):
+            eq(got, ref[name], name)
+        assert r.rounds == rounds
