@@ -419,7 +419,7 @@ CSTONE_API cstone_status cstone_focus_mac(const uint64_t* node_keys, size_t n_no
  *               particles);
  *   size class  floor(log2 n);
  *   device      the current HIP device's architecture and compute-unit count.
- * Without an entry the built-in shape (index 0) is used. Every shape gives
+ * Without an entry the built-in shape for the size is used. Every shape gives
  * the same result (the sort is stable), so the table changes speed only.
  * The table is the library's only process-wide state; its calls are
  * thread-safe, and a sort already started keeps the shape it looked up.

@@ -225,7 +225,7 @@ CSTONE_API cstone_status cstone_batch_create(const cstone_set* sets, uint32_t n_
         p->max_tiles = std::max<uint64_t>(p->max_tiles, cs::tiles_for(*p, v));
     {  // the autotune table's shape for a batch of this many keys, else the built-in one
         const int tuned = cs::tune_lookup(cs::kTuneBatchSort, p->n_total);
-        p->variant = tuned >= 0 ? tuned : cs::sort_builtin_variant();
+        p->variant = tuned >= 0 ? tuned : cs::sort_builtin_variant(SIZE_MAX);  // (a launch covers many sets)
     }
     cs::make_tiles(*p);
     *plan = p;

@@ -37,7 +37,7 @@ size_t sort_workspace_bytes(size_t n, bool with_perm);
 // overflow), all above the public CSTONE_FLAG_* bits.
 // variant: the sort shape (sort_variant_count() of them); -1 takes the shape
 // of the autotune table for a particle-key sort of n keys (with perm, 63
-// bits), else the built-in one. A prepared sort must name the shape its
+// bits), else the built-in one for n. A prepared sort must name the shape its
 // set-up used.
 cstone_status launch_sort(const uint64_t* keys_in, uint64_t* keys_out, uint32_t* perm_out, size_t n,
                           int sig_bits, void* ws, size_t ws_bytes, hipStream_t stream,
@@ -115,7 +115,7 @@ struct SortVariantInfo {
 cstone_status set_lookback_patience(uint32_t waits);
 int sort_variant_count();
 SortVariantInfo sort_variant_info(int variant);
-int sort_builtin_variant();  // the shape used where the autotune table has no entry
+int sort_builtin_variant(size_t n);  // the shape for n keys where the autotune table has no entry
 
 // tune.hip — the autotune table: (kernel, floor(log2 n), device) -> shape
 constexpr int kTuneSort = 0;       // particle-key sort of cstone_sort / cstone_build

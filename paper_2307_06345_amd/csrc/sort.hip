@@ -1318,17 +1318,25 @@ struct Variant {
 // CU. The 9-bit shapes without the split run 7 plain LSD passes, which a
 // strongly clustered set (many level-9 buckets over the bucket kernel's
 // sizes) can favour.
-const Variant kVariants[] = {
+constexpr Variant kVariants[] = {
     CS_VARIANT(9, 512, 16, 4, true),  CS_VARIANT(8, 512, 16, 4, false), CS_VARIANT(9, 512, 12, 4, true),
     CS_VARIANT(9, 512, 32, 4, true),  CS_VARIANT(9, 1024, 8, 4, true),  CS_VARIANT(9, 1024, 16, 4, true),
     CS_VARIANT(8, 256, 16, 4, false), CS_VARIANT(9, 512, 16, 4, false), CS_VARIANT(9, 512, 12, 4, false),
+    CS_VARIANT(9, 512, 4, 4, true),   CS_VARIANT(9, 512, 8, 4, true),
 };
 #undef CS_VARIANT
 constexpr int kNumVariants = sizeof(kVariants) / sizeof(kVariants[0]);
 
-// Shape used where the autotune table has no entry: 9-bit digits, 512 x 16
-// tiles, the split sort.
+// Shapes used where the autotune table has no entry: 9-bit digits, the split
+// sort, 512 x 16 tiles; short sorts take smaller tiles, since a pass over few
+// tiles lasts as long as one of them (16 ballots a digit bit one after another)
+// and leaves most CUs idle. Builds with 512 x 16 / 8 / 4 tiles: 1500 Plummer
+// particles 109 / 98 / 93 us, 65,536 uniform 116 / 106 / 104, 2^18 133 / 125 /
+// 120, 591,351 145 / 140 / 145, 2^20 171 / 167 / 178, 2^21 196 / 196 / 224.
 constexpr int kBuiltinVariant = 0;
+constexpr int kSmallVariant = 9, kMediumVariant = 10;
+constexpr size_t kSmallSort = size_t{1} << 18, kMediumSort = size_t{1} << 20;
+static_assert(kVariants[kSmallVariant].items == 4 && kVariants[kMediumVariant].items == 8, "the small tiles");
 
 // Split sorts of particle keys: 9-bit digits, the top three first (the
 // level-9 octant), before them the digit below if the keys crowd, then four low
@@ -1401,7 +1409,7 @@ bool use_split(size_t n, int sig_bits, bool with_perm, const Variant& var) {
 
 size_t sort_workspace_bytes(size_t n, bool with_perm) { return carve_sort(nullptr, n, with_perm).bytes; }
 
-int sort_builtin_variant() { return kBuiltinVariant; }
+int sort_builtin_variant(size_t n) { return n <= kSmallSort ? kSmallVariant : n <= kMediumSort ? kMediumVariant : kBuiltinVariant; }
 
 namespace {
 const Variant& variant_or_builtin(int v) { return kVariants[v >= 0 && v < kNumVariants ? v : kBuiltinVariant]; }

@@ -91,7 +91,7 @@ void tune_record(int kernel, size_t n, int variant) {
 
 int sort_resolve_variant(size_t n) {
     const int v = tune_lookup(kTuneSort, n);
-    return v >= 0 ? v : sort_builtin_variant();
+    return v >= 0 ? v : sort_builtin_variant(n);
 }
 
 }  // namespace cs
