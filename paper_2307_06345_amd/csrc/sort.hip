@@ -1330,9 +1330,11 @@ constexpr int kNumVariants = sizeof(kVariants) / sizeof(kVariants[0]);
 // Shapes used where the autotune table has no entry: 9-bit digits, the split
 // sort, 512 x 16 tiles; short sorts take smaller tiles, since a pass over few
 // tiles lasts as long as one of them (16 ballots a digit bit one after another)
-// and leaves most CUs idle. Builds with 512 x 16 / 8 / 4 tiles: 1500 Plummer
-// particles 109 / 98 / 93 us, 65,536 uniform 116 / 106 / 104, 2^18 133 / 125 /
-// 120, 591,351 145 / 140 / 145, 2^20 171 / 167 / 178, 2^21 196 / 196 / 224.
+// and leaves most CUs idle. Builds back to back with 512 x 16 / 8 / 4 tiles:
+// 1500 Plummer particles 109 / 98 / 93 us, uniform ones 65,536 116 / 106 / 104,
+// 2^18 133 / 125 / 120, 591,351 145 / 140 / 145, 2^20 171 / 167 / 178, 2^21 196
+// / 196 / 224. By turns with the 512 x 16 tiles on fresh inputs: 1500 105 -> 94
+// us, 65,536 117 -> 111, 591,351 Plummer 183 both.
 constexpr int kBuiltinVariant = 0;
 constexpr int kSmallVariant = 9, kMediumVariant = 10;
 constexpr size_t kSmallSort = size_t{1} << 18, kMediumSort = size_t{1} << 20;
