@@ -16,7 +16,7 @@
 // only if it fails the minimum-distance MAC against F and also merges a group
 // of 8 sibling leaves whose parent passes it. The MAC of a node is evaluated
 // against F cut into maximal aligned key blocks (at most 2 x 7 per level),
-// whose grid boxes the host computes once and the kernel holds in LDS.
+// whose grid boxes every block finds by itself and holds in LDS.
 //
 // The partition (Sec. 6) groups the leaves into n_ranks bins of consecutive
 // leaves with about N / n_ranks particles each: bin r starts at the first
@@ -24,8 +24,10 @@
 #include <algorithm>
 #include <cmath>
 
+#include <type_traits>
+
 #include "common.hpp"
-#include "hilbert.hpp"
+#include "focus.hpp"
 #include "internal.hpp"
 
 namespace cs {
@@ -57,38 +59,7 @@ __global__ __launch_bounds__(kGBlock) void shard_reduce_kernel(const uint32_t* _
     N[i] = sum;
 }
 
-// Minimum-distance MAC of the node (corner, edge) against the focus blocks:
-// fails iff some block lies within l / theta, tested as r^2 theta^2 <= l^2
-// with r^2 exact (integer grid) and one rounding in the product.
-__device__ __forceinline__ bool mac_fails_dev(const uint32_t c[3], uint32_t edge, const uint4* blocks,
-                                              uint32_t nblocks, double theta2) {
-    const double l2 = static_cast<double>(edge) * static_cast<double>(edge);
-    for (uint32_t b = 0; b < nblocks; ++b) {
-        const uint4 f = blocks[b];
-        const uint32_t fl[3] = {f.x, f.y, f.z};
-        uint64_t r2 = 0;
-#pragma unroll
-        for (int d = 0; d < 3; ++d) {
-            const int64_t a0 = c[d], a1 = static_cast<int64_t>(c[d]) + edge;
-            const int64_t b0 = fl[d], b1 = static_cast<int64_t>(fl[d]) + f.w;
-            const int64_t gap = b0 > a1 ? b0 - a1 : (a0 > b1 ? a0 - b1 : 0);
-            r2 += static_cast<uint64_t>(gap * gap);
-        }
-        if (!(static_cast<double>(r2) * theta2 > l2)) return true;
-    }
-    return false;
-}
-
-struct FocusSpec {
-    const uint4* blocks;  // {corner x, y, z, edge} of the focus blocks
-    uint32_t nblocks;
-    int curve;
-    double theta2;
-};
-
-constexpr uint32_t kMaxFocusBlocks = 320;  // 2 x 7 x 21 = 294 at most
-
-__device__ __forceinline__ int level_of_delta(uint64_t delta) {  // delta = 8^(L - level)
+__device__ __forceinline__ uint32_t level_of_delta(uint64_t delta) {  // delta = 8^(L - level)
     return kL - (63 - clz64(delta)) / 3;
 }
 
@@ -102,11 +73,9 @@ __global__ __launch_bounds__(kGBlock) void global_decide_kernel(const uint64_t* 
                                                                 const uint32_t* __restrict__ N, uint32_t nl,
                                                                 uint32_t n_crit, uint32_t* __restrict__ O,
                                                                 uint32_t* changed, FocusSpec focus) {
-    __shared__ uint4 fb[FOCUS ? kMaxFocusBlocks : 1];
-    __shared__ uint16_t dec[FOCUS ? kStates * 8 : 1];
+    __shared__ std::conditional_t<FOCUS, FocusSmem, uint32_t> fsm;
     if constexpr (FOCUS) {
-        for (uint32_t b = threadIdx.x; b < focus.nblocks; b += kGBlock) fb[b] = focus.blocks[b];
-        for (uint32_t e = threadIdx.x; e < kStates * 8; e += kGBlock) dec[e] = kHilbertDecode.dec[e];
+        focus_fill(focus, fsm);
         __syncthreads();
     }
     const uint32_t i = blockIdx.x * kGBlock + threadIdx.x;
@@ -119,12 +88,7 @@ __global__ __launch_bounds__(kGBlock) void global_decide_kernel(const uint64_t* 
     uint32_t op = 1;
     bool split = N[i] > n_crit && delta > 1;
     if constexpr (FOCUS) {
-        if (split) {
-            uint32_t c[3];
-            const int level = level_of_delta(delta);
-            node_corner(k, level, focus.curve, dec, c);
-            split = mac_fails_dev(c, 1u << (kL - level), fb, focus.nblocks, focus.theta2);
-        }
+        if (split) split = node_fails(k, level_of_delta(delta), focus, fsm);
     }
     if (split) {
         op = 8;
@@ -135,12 +99,8 @@ __global__ __launch_bounds__(kGBlock) void global_decide_kernel(const uint64_t* 
             for (uint32_t m = 0; m < 8; ++m) group += N[i - j + m];
             bool merge = group <= n_crit;
             if constexpr (FOCUS) {
-                if (!merge) {  // the parent passes the MAC
-                    uint32_t c[3];
-                    const int plevel = level_of_delta(delta) - 1;
-                    node_corner(K[i - j], plevel, focus.curve, dec, c);
-                    merge = !mac_fails_dev(c, 1u << (kL - plevel), fb, focus.nblocks, focus.theta2);
-                }
+                // the parent passes the MAC
+                if (!merge) merge = !node_fails(K[i - j], level_of_delta(delta) - 1, focus, fsm);
             }
             if (merge) op = 0;
         }
@@ -153,19 +113,15 @@ __global__ __launch_bounds__(kGBlock) void global_decide_kernel(const uint64_t* 
 // it fails against the focus range.
 __global__ __launch_bounds__(kGBlock) void focus_mac_kernel(const uint64_t* __restrict__ NK, uint32_t n,
                                                             FocusSpec focus, uint8_t* __restrict__ fails) {
-    __shared__ uint4 fb[kMaxFocusBlocks];
-    __shared__ uint16_t dec[kStates * 8];
-    for (uint32_t b = threadIdx.x; b < focus.nblocks; b += kGBlock) fb[b] = focus.blocks[b];
-    for (uint32_t e = threadIdx.x; e < kStates * 8; e += kGBlock) dec[e] = kHilbertDecode.dec[e];
+    __shared__ FocusSmem fsm;
+    focus_fill(focus, fsm);
     __syncthreads();
     const uint32_t p = blockIdx.x * kGBlock + threadIdx.x;
     if (p >= n) return;
     const uint64_t key = NK[p];
     const int level = (63 - clz64(key)) / 3;
     const uint64_t start = (key ^ (1ull << (3 * level))) << (3 * (kL - level));
-    uint32_t c[3];
-    node_corner(start, level, focus.curve, dec, c);
-    fails[p] = mac_fails_dev(c, 1u << (kL - level), fb, focus.nblocks, focus.theta2) ? 1 : 0;
+    fails[p] = node_fails(start, level, focus, fsm) ? 1 : 0;
 }
 
 // g3 (Eqs. rebalancecopy, rebalancesplit) into K_out, unless the new array
@@ -309,22 +265,6 @@ cstone_status run_rounds(const uint64_t* P, const uint64_t* shard_off_dev, uint3
     return status;
 }
 
-// The focus range [fa, fb) as maximal aligned key blocks, each as its grid
-// box {corner x, y, z, edge}.
-uint32_t focus_blocks(uint64_t fa, uint64_t fb, int curve, uint4* out) {
-    uint32_t nb = 0;
-    uint64_t k = fa;
-    while (k < fb) {
-        int e = kL;  // the block 8^e: aligned at k and ending by fb
-        while (e > 0 && ((k & ((1ull << (3 * e)) - 1)) != 0 || fb - k < (1ull << (3 * e)))) --e;
-        uint32_t c[3];
-        node_corner(k, kL - e, curve, kHilbertDecode.dec, c);
-        out[nb++] = make_uint4(c[0], c[1], c[2], 1u << e);
-        k += 1ull << (3 * e);
-    }
-    return nb;
-}
-
 }  // namespace
 
 cstone_status run_global_rebalance(const uint64_t* P, const uint64_t* shard_off_dev, uint32_t G, uint32_t n_crit,
@@ -335,53 +275,63 @@ cstone_status run_global_rebalance(const uint64_t* P, const uint64_t* shard_off_
                       nullptr, stream);
 }
 
-size_t focus_workspace_bytes(size_t leaf_capacity) {
+// The focused tree comes from the sorted keys directly (tree.hip), if so many
+// rounds are allowed and n is at most kFocusDirect: one pass over the keys, 16
+// B a particle, replaces the rounds' searches, launches and waits for the host.
+// 4 M Plummer particles, N_crit 32, one of 64 ranges, with links and the nodes'
+// MAC: 1000 -> 200 us. A round takes about 100 us whatever n, the pass some 3 us
+// per million particles, so from a tree that one round adapts it is not the
+// faster one above some 30 M, and from the root (8 to 10 rounds) not above 300 M.
+constexpr size_t kFocusDirect = size_t{1} << 25, kFocusDirectRoot = size_t{1} << 27;
+
+namespace {
+size_t focus_rounds_bytes(size_t leaf_capacity) {
     Carve c(nullptr);
     c.take<uint64_t>(2);
-    c.take<uint4>(kMaxFocusBlocks);
     return c.off + global_rebalance_workspace_bytes(leaf_capacity, 1);
+}
+}  // namespace
+
+size_t focus_workspace_bytes(size_t leaf_capacity) {
+    return std::max(focus_rounds_bytes(leaf_capacity),
+                    leaf_capacity ? focus_tree_workspace_bytes(kFocusDirectRoot, leaf_capacity) : 0);
 }
 
 cstone_status run_focus_rebalance(const uint64_t* P, size_t n, uint32_t n_crit, int curve, uint64_t fa, uint64_t fb,
                                   double theta, uint64_t* leaves, size_t* n_leaves, size_t cap, uint32_t* counts,
                                   uint32_t max_iters, uint32_t* iters_done, void* ws, size_t ws_bytes,
                                   hipStream_t stream) {
-    if (ws_bytes < focus_workspace_bytes(cap)) return CSTONE_ERR_INVALID_ARG;
+    if (ws_bytes < focus_rounds_bytes(cap)) return CSTONE_ERR_INVALID_ARG;
+    const FocusSpec f{fa, fb, curve, theta * theta};
+    if (tree_possible(n, max_iters) && n <= (*n_leaves > 1 ? kFocusDirect : kFocusDirectRoot)) {
+        TreePass tree;
+        if (tree.run(P, n, n_crit, leaves, *n_leaves, cap, counts, nullptr, nullptr, nullptr, ws, ws_bytes, nullptr,
+                     nullptr, nullptr, stream, &f)) {
+            bool fits = false;
+            const cstone_status s = tree.wait(&fits);
+            if (s != CSTONE_OK) return s;
+            if (fits) {
+                *n_leaves = tree.n_leaves;
+                if (iters_done) *iters_done = tree.rounds;
+                return CSTONE_OK;
+            }
+        }
+    }
     Carve c(ws);
     uint64_t* off = c.take<uint64_t>(2);
-    uint4* blocks = c.take<uint4>(kMaxFocusBlocks);
     const uint64_t host_off[2] = {0, n};
-    uint4 host_blocks[kMaxFocusBlocks];
-    FocusSpec f{};
-    f.blocks = blocks;
-    f.nblocks = focus_blocks(fa, fb, curve, host_blocks);
-    f.curve = curve;
-    f.theta2 = theta * theta;
     CS_HIP(hipMemcpyAsync(off, host_off, sizeof host_off, hipMemcpyHostToDevice, stream));
-    if (f.nblocks)
-        CS_HIP(hipMemcpyAsync(blocks, host_blocks, f.nblocks * sizeof(uint4), hipMemcpyHostToDevice, stream));
     return run_rounds(P, off, 1, n_crit, leaves, n_leaves, cap, counts, max_iters, iters_done,
                       static_cast<char*>(ws) + c.off, ws_bytes - c.off, &f, stream);
 }
 
-size_t focus_mac_workspace_bytes() {
-    Carve c(nullptr);
-    c.take<uint4>(kMaxFocusBlocks);
-    return c.off;
-}
+// What callers have to pass, as they always had; nothing is kept in it.
+size_t focus_mac_workspace_bytes() { return kMaxFocusBlocks * sizeof(uint4); }
 
 cstone_status launch_focus_mac(const uint64_t* node_keys, size_t n_nodes, int curve, uint64_t fa, uint64_t fb,
                                double theta, uint8_t* fails, void* ws, size_t ws_bytes, hipStream_t stream) {
-    if (ws_bytes < focus_mac_workspace_bytes()) return CSTONE_ERR_INVALID_ARG;
-    uint4 host_blocks[kMaxFocusBlocks];
-    FocusSpec f{};
-    f.blocks = static_cast<uint4*>(ws);
-    f.nblocks = focus_blocks(fa, fb, curve, host_blocks);
-    f.curve = curve;
-    f.theta2 = theta * theta;
-    if (f.nblocks)
-        CS_HIP(hipMemcpyAsync(static_cast<uint4*>(ws), host_blocks, f.nblocks * sizeof(uint4), hipMemcpyHostToDevice,
-                              stream));
+    if (!ws || ws_bytes < focus_mac_workspace_bytes()) return CSTONE_ERR_INVALID_ARG;
+    const FocusSpec f{fa, fb, curve, theta * theta};
     if (n_nodes)
         hipLaunchKernelGGL(focus_mac_kernel, dim3(grid_of(n_nodes)), dim3(kGBlock), 0, stream, node_keys,
                            static_cast<uint32_t>(n_nodes), f, fails);

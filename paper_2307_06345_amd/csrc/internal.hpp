@@ -205,6 +205,8 @@ bool tree_possible(size_t n, uint32_t max_iters);
 
 // The whole rebalance loop of one set, and its links (unless node_keys is
 // NULL), enqueued without a host synchronisation.
+struct FocusSpec;
+size_t focus_tree_workspace_bytes(size_t n, size_t cap);
 class TreePass {
 public:
     // From the root (nl0 == 1) or, with the rounds counted from it, from the
@@ -212,7 +214,9 @@ public:
     // False (nothing enqueued) if ws is too short.
     bool run(const uint64_t* sorted_keys, size_t n, uint32_t n_crit, uint64_t* leaves, size_t nl0, size_t cap,
              uint32_t* counts, uint64_t* node_keys, uint32_t* child, uint32_t* level_offsets, void* ws, size_t ws_bytes,
-             TreeState* cleared, const uint32_t* input_flags, const uint32_t* listed, hipStream_t stream);
+             TreeState* cleared, const uint32_t* input_flags, const uint32_t* listed, hipStream_t stream,
+             const FocusSpec* focus = nullptr);
+    // focus: the tree focused on its range (node_keys NULL); ws: focus_tree_workspace_bytes.
     // listed: NULL, or the word that says whether the keys' sort is incomplete
     // (see sort_listed_word); `leaves` is then left alone unless from the root.
     // Synchronises. *fits false: the tree or a round on the way to it exceeds

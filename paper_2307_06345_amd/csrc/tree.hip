@@ -26,9 +26,18 @@
 // most, and from the root it takes depth rounds and the check round; from
 // another array, 1 + the largest level difference between two overlapping
 // leaves of the two arrays.
+//
+// The tree focused on a range of the curve (Sec. 7) is the same with fewer
+// internal nodes, those that fail the MAC too. A node that fails has only
+// ancestors that fail (they are larger and no farther), so the mark launch ends
+// each particle's levels before the first that passes, and the write launch
+// looks for their children in the list too. With few internal nodes the
+// particles' bytes are neither kept nor read.
 #include <algorithm>
+#include <type_traits>
 
 #include "common.hpp"
+#include "focus.hpp"
 #include "internal.hpp"
 
 namespace cs {
@@ -106,6 +115,10 @@ __device__ __forceinline__ uint64_t from_lane_before(uint64_t v) {  // lane 0 ge
            static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(lo), 0x138, 0xf, 0xf, false));
 }
 
+struct NoFocus {};
+template <bool FOCUS>
+using FocusPart = std::conditional_t<FOCUS, FocusSmem, NoFocus>;
+
 struct MarkSmem {
     uint32_t list[kTreeTile];     // per wave: its particles that start internal nodes: place | u << 12 | e << 17
     uint32_t level[kTreeLevels];  // internal nodes of the tile per level
@@ -127,8 +140,8 @@ struct MarkSmem {
 // One wave's 512 particles from place wbase of the tile on: their bytes, and
 // the list of those that start internal nodes (in order; returns how many).
 // FULL: every key that is read exists; otherwise keys past the end read the
-// last key and are masked.
-template <bool FULL>
+// last key and are masked. BYTES: the particles' bytes are kept.
+template <bool FULL, bool BYTES>
 __device__ __forceinline__ uint32_t mark_wave(const uint64_t* __restrict__ Ps, uint32_t base, uint32_t wbase, uint32_t n,
                                               uint32_t N, uint32_t max_level, uint8_t* __restrict__ below,
                                               uint32_t* mylist) {
@@ -165,10 +178,10 @@ __device__ __forceinline__ uint32_t mark_wave(const uint64_t* __restrict__ Ps, u
         const uint32_t e = min(common_digits(a[it], b[it]), max_level) + 1u;
         bool start = e > u;
         if constexpr (FULL) {
-            out[it * kWave] = static_cast<uint8_t>(u);
+            if constexpr (BYTES) out[it * kWave] = static_cast<uint8_t>(u);
         } else {
             const uint64_t j = static_cast<uint64_t>(first) + it * kWave + lane;
-            if (j < n) out[it * kWave] = static_cast<uint8_t>(u);
+            if (BYTES && j < n) out[it * kWave] = static_cast<uint8_t>(u);
             start = start && j + N < n;
         }
         const uint64_t m = __ballot(start);
@@ -180,7 +193,9 @@ __device__ __forceinline__ uint32_t mark_wave(const uint64_t* __restrict__ Ps, u
     return starts;
 }
 
-template <bool BATCH>
+// FOCUS (one set): a tile has no slots of its own, since most hold none of the
+// few internal nodes; those that do take a run of the shared ones.
+template <bool BATCH, bool FOCUS>
 __global__ __launch_bounds__(kMarkBlock) void tree_mark_kernel(const uint64_t* __restrict__ P, TreeOne one,
                                                                const BatchSet* __restrict__ sets,
                                                                const uint32_t* __restrict__ tile_set, uint32_t n_tiles,
@@ -188,8 +203,10 @@ __global__ __launch_bounds__(kMarkBlock) void tree_mark_kernel(const uint64_t* _
                                                                uint64_t* __restrict__ inodes,
                                                                uint32_t* __restrict__ ipos,
                                                                uint64_t* __restrict__ tile_off,
-                                                               uint32_t* __restrict__ rows, uint32_t* reserved) {
+                                                               uint32_t* __restrict__ rows, uint32_t* reserved,
+                                                               FocusSpec focus) {
     __shared__ MarkSmem sm;
+    __shared__ FocusPart<FOCUS> fsm;
     const uint32_t tid = threadIdx.x, lane = lane_id();
     const uint32_t wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     const uint32_t gtile = blockIdx.x;
@@ -208,12 +225,26 @@ __global__ __launch_bounds__(kMarkBlock) void tree_mark_kernel(const uint64_t* _
     const uint32_t base = tile * kTreeTile;
     const uint32_t wbase = wave * kMarkItems * kWave;  // the wave's first place
     if (tid < kTreeLevels) sm.level[tid] = 0;
-    if (tid == 0 && gtile + 1 == n_tiles) below[n] = 0;
+    if (!FOCUS && tid == 0 && gtile + 1 == n_tiles) below[n] = 0;
     const bool full = static_cast<uint64_t>(base) + kTreeTile + N <= n;  // block-uniform: every key exists
     uint32_t* mylist = sm.list + wbase;
-    const uint32_t starts = full ? mark_wave<true>(Ps, base, wbase, n, N, max_level, below, mylist)
-                                 : mark_wave<false>(Ps, base, wbase, n, N, max_level, below, mylist);
-    __syncthreads();  // sm.level is cleared
+    const uint32_t starts = full ? mark_wave<true, !FOCUS>(Ps, base, wbase, n, N, max_level, below, mylist)
+                                 : mark_wave<false, !FOCUS>(Ps, base, wbase, n, N, max_level, below, mylist);
+    if constexpr (FOCUS) {
+        if (__syncthreads_or(static_cast<int>(starts))) {  // block-uniform; sm.level is cleared
+            focus_fill(focus, fsm);
+            __syncthreads();
+            for (uint32_t r = lane; r < starts; r += kWave) {  // (the wave's own places)
+                const uint32_t x = mylist[r], u = (x >> 12) & 31u, e = x >> 17;
+                const uint64_t key = Ps[base + (x & 0xfffu)];
+                uint32_t l = u;
+                while (l < e && node_fails(key, l, focus, fsm)) ++l;
+                mylist[r] = (x & 0x1ffffu) | (l << 17);
+            }
+        }
+    } else {
+        __syncthreads();  // sm.level is cleared
+    }
     // internal nodes of the wave, per level and in all
     uint32_t mine = 0;
     for (uint32_t r = lane; r < starts; r += kWave) {
@@ -234,7 +265,7 @@ __global__ __launch_bounds__(kMarkBlock) void tree_mark_kernel(const uint64_t* _
     if (tid < kTreeRows) rows[static_cast<size_t>(tid) * n_tiles + gtile] = tid < kTreeLevels ? sm.level[tid] : total;
     if (total == 0) return;  // block-uniform
     // the tile's own slots, or a run of the set's shared ones after them
-    const uint32_t own = tile_slots(N);
+    const uint32_t own = FOCUS ? 0u : tile_slots(N);
     const uint64_t shared = static_cast<uint64_t>(own) * tree_tiles_of(n);
     const uint64_t slots = shared + (o.cap - 1) / 7 + 1;
     uint64_t at = static_cast<uint64_t>(tile) * own;
@@ -377,7 +408,7 @@ constexpr int kWriteWaves = kWriteBlock / kWave;
 // and three dependent reads (list, bytes, keys of the children's starts); 24 B
 // of K, counts, NK and CO are written per leaf.
 constexpr uint32_t kByteMaxCrit = 256;  // above it the bytes of 8 N particles are too many round trips: all search
-template <bool BATCH>
+template <bool BATCH, bool FOCUS>
 __global__ __launch_bounds__(kWriteBlock) void tree_write_kernel(const uint64_t* __restrict__ P, TreeOne one,
                                                                  const BatchSet* __restrict__ sets,
                                                                  const uint32_t* __restrict__ tile_set,
@@ -392,7 +423,8 @@ __global__ __launch_bounds__(kWriteBlock) void tree_write_kernel(const uint64_t*
                                                                  uint64_t* __restrict__ nk, uint32_t* __restrict__ co,
                                                                  uint32_t* __restrict__ lo_out, TreeState* st,
                                                                  const uint32_t* input_flags, const uint32_t* listed,
-                                                                 TreeResults res) {
+                                                                 TreeResults res, FocusSpec focus) {
+    __shared__ FocusPart<FOCUS> fsm;
     __shared__ uint32_t before[kTreeRows], after[kTreeRows], totals[kTreeRows];
     __shared__ uint32_t found[kWriteWaves][kWave];  // per wave and group: particles that start children
     __shared__ uint64_t first_key[kWriteWaves][kWave];  // per wave: the chunk's nodes' first keys and particles
@@ -495,7 +527,11 @@ __global__ __launch_bounds__(kWriteBlock) void tree_write_kernel(const uint64_t*
     const uint64_t* Ps = P + o.first;
     const uint32_t p0 = before[kTreeLevels];
     const uint32_t here = after[kTreeLevels] - before[kTreeLevels];  // internal nodes of this tile
-    if (here == 0) return;
+    if (here == 0) return;  // block-uniform
+    if constexpr (FOCUS) {
+        focus_fill(focus, fsm);
+        __syncthreads();
+    }
     const uint64_t* In = inodes + o.inode_off;
     const uint32_t* Ip = ipos + o.inode_off;
     const uint64_t list = tile_off[gtile];
@@ -541,7 +577,7 @@ __global__ __launch_bounds__(kWriteBlock) void tree_write_kernel(const uint64_t*
         bool leafy = false;
         {
             const uint32_t next = __shfl_down(level, 1, kWave);
-            if (N <= kByteMaxCrit && base + lane + 1 < here) {
+            if (!FOCUS && N <= kByteMaxCrit && base + lane + 1 < here) {
                 const uint32_t nlv = lane + 1 < kWave
                                          ? next
                                          : static_cast<uint32_t>(63 - clz64(In[list + base + kWave])) / 3u;
@@ -569,6 +605,7 @@ __global__ __launch_bounds__(kWriteBlock) void tree_write_kernel(const uint64_t*
             const uint64_t ck = (kx << 3) | c;        // this lane's child
             uint32_t b;  // lane c: the first particle of child c or after it; lane 0: the node's end
             bool inner = false;
+            uint32_t next_q = 0;  // place in the chunk of the first node in or after this child
             uint32_t ahead = 0;  // internal nodes below this one that start before this child, if the chunk says so
             if (bytes) {
                 const uint32_t le_l = (l * 0x01010101u) | 0x80808080u, le_n = le_l + 0x01010101u;
@@ -646,6 +683,7 @@ __global__ __launch_bounds__(kWriteBlock) void tree_write_kernel(const uint64_t*
                         q_hi = mid;
                 }
                 ahead = q < chunk ? q - x - 1 : 0xffffffffu;
+                next_q = c ? q : x + 1;
                 uint32_t lo_at = on ? first_at[wave][q - 1] : 0u, hi_at = lo_at;
                 if (on && q < chunk) {
                     hi_at = first_at[wave][q];
@@ -677,6 +715,16 @@ __global__ __launch_bounds__(kWriteBlock) void tree_write_kernel(const uint64_t*
             const uint32_t cnt = next - from;
             if (!bytes) {
                 inner = on && l + 1 <= max_level && cnt > N;
+                if constexpr (FOCUS) {
+                    // the child is internal if nodes of the list lie in it; past
+                    // the chunk the MAC has to say (the MAC for all: 78 us, now 38)
+                    if (inner) {
+                        const uint64_t start = (ck ^ (1ull << (3 * (l + 1)))) << shift;
+                        inner = next_q < min(here - base, static_cast<uint32_t>(kWave))
+                                    ? first_key[wave][next_q] < start + (1ull << shift)
+                                    : node_fails(start, l + 1, focus, fsm);
+                    }
+                }
                 const bool family = ((__ballot(inner) >> group) & 0xffull) != 0;
                 if (on && !inner && c && ahead != 0xffffffffu) {
                     at += 7u * ahead;
@@ -859,10 +907,10 @@ struct TreeWs {
     size_t bytes;
 };
 
-TreeWs carve_tree(void* ws, size_t n, uint32_t n_crit, size_t cap, bool incremental) {
+TreeWs carve_tree(void* ws, size_t n, uint32_t n_crit, size_t cap, bool incremental, bool focus) {
     Carve c(ws);
     TreeWs w{};
-    const size_t tiles = tree_tiles(n), slots = tree_slots(n, n_crit, cap);
+    const size_t tiles = tree_tiles(n), slots = focus ? (cap - 1) / 7 + 1 : tree_slots(n, n_crit, cap);
     w.st = c.take<TreeState>(1);
     w.K_new = incremental ? c.take<uint64_t>(cap + 1) : nullptr;
     w.inodes = c.take<uint64_t>(slots);
@@ -870,7 +918,7 @@ TreeWs carve_tree(void* ws, size_t n, uint32_t n_crit, size_t cap, bool incremen
     w.tile_off = c.take<uint64_t>(tiles);
     w.rows = c.take<uint32_t>(kTreeRows * tiles);
     w.totals = c.take<uint32_t>(kTreeRows);
-    w.below = c.take<uint8_t>(n + kBytesPad);
+    w.below = focus ? nullptr : c.take<uint8_t>(n + kBytesPad);
     w.bytes = c.off;
     return w;
 }
@@ -880,8 +928,10 @@ __global__ void tree_clear_kernel(TreeState* st) { *st = TreeState{}; }
 }  // namespace
 
 size_t tree_workspace_bytes(size_t n, uint32_t n_crit, size_t cap, bool incremental) {
-    return carve_tree(nullptr, n, n_crit, cap, incremental).bytes;
+    return carve_tree(nullptr, n, n_crit, cap, incremental, false).bytes;
 }
+
+size_t focus_tree_workspace_bytes(size_t n, size_t cap) { return carve_tree(nullptr, n, 1, cap, true, true).bytes; }
 
 size_t tree_tiles(size_t n) { return tree_tiles_of(n); }
 
@@ -894,9 +944,9 @@ bool tree_possible(size_t n, uint32_t max_iters) {
 bool TreePass::run(const uint64_t* P, size_t n, uint32_t n_crit, uint64_t* leaves, size_t nl0, size_t cap,
                    uint32_t* counts, uint64_t* node_keys, uint32_t* child, uint32_t* level_offsets, void* ws,
                    size_t ws_bytes, TreeState* cleared, const uint32_t* input_flags, const uint32_t* listed,
-                   hipStream_t stream) {
+                   hipStream_t stream, const FocusSpec* focus) {
     incremental_ = nl0 > 1;
-    const TreeWs w = carve_tree(ws, n, n_crit, cap, incremental_);
+    const TreeWs w = carve_tree(ws, n, n_crit, cap, incremental_, focus != nullptr);
     if (ws_bytes < w.bytes || cap >= 0xffffffffull) return false;
     stream_ = stream;
     st_ = cleared ? cleared : w.st;
@@ -908,14 +958,17 @@ bool TreePass::run(const uint64_t* P, size_t n, uint32_t n_crit, uint64_t* leave
     const uint32_t* no_table = nullptr;
     constexpr uint32_t max_level = kL - 1;
     uint64_t* K = incremental_ ? w.K_new : leaves;
-    hipLaunchKernelGGL(tree_mark_kernel<false>, dim3(tiles), dim3(kMarkBlock), 0, stream, P, one, no_sets, no_table,
-                       tiles, max_level, w.below, w.inodes, w.ipos, w.tile_off, w.rows, &st_->reserved);
+    const auto mark = focus ? tree_mark_kernel<false, true> : tree_mark_kernel<false, false>;
+    const auto write = focus ? tree_write_kernel<false, true> : tree_write_kernel<false, false>;
+    const FocusSpec spec = focus ? *focus : FocusSpec{};
+    hipLaunchKernelGGL(mark, dim3(tiles), dim3(kMarkBlock), 0, stream, P, one, no_sets, no_table, tiles, max_level,
+                       w.below, w.inodes, w.ipos, w.tile_off, w.rows, &st_->reserved, spec);
     if (scanned)
         hipLaunchKernelGGL(tree_scan_kernel<false>, dim3(kTreeRows), dim3(kScanBlock), 0, stream, no_sets, tiles, w.rows,
                            w.totals);
-    hipLaunchKernelGGL(tree_write_kernel<false>, dim3(tiles), dim3(kWriteBlock), 0, stream, P, one, no_sets, no_table,
-                       tiles, max_level, w.inodes, w.ipos, w.tile_off, w.below, w.rows, scanned, w.totals, K, counts,
-                       node_keys, child, level_offsets, st_, input_flags, listed, TreeResults{});
+    hipLaunchKernelGGL(write, dim3(tiles), dim3(kWriteBlock), 0, stream, P, one, no_sets, no_table, tiles, max_level,
+                       w.inodes, w.ipos, w.tile_off, w.below, w.rows, scanned, w.totals, K, counts, node_keys, child,
+                       level_offsets, st_, input_flags, listed, TreeResults{}, spec);
     if (incremental_) {
         const uint32_t grid = static_cast<uint32_t>(std::min<size_t>((cap + kCmpTile - 1) / kCmpTile, 1024));
         hipLaunchKernelGGL(tree_compare_kernel, dim3(grid), dim3(kCmpBlock), 0, stream, leaves,
@@ -985,15 +1038,16 @@ cstone_status launch_batch_tree(const uint64_t* P, size_t n_total, const BatchSe
     const TreeResults res{rounds, set_flags, sort_err, results};
     if (tiles) {
         const bool scanned = max_tiles > kDirectTiles;
-        hipLaunchKernelGGL(tree_mark_kernel<true>, dim3(tiles), dim3(kMarkBlock), 0, stream, P, one, sets, tile_set,
-                           tiles, max_level, w.below, w.inodes, w.ipos, w.tile_off, w.rows, reserved);
+        hipLaunchKernelGGL((tree_mark_kernel<true, false>), dim3(tiles), dim3(kMarkBlock), 0, stream, P, one, sets,
+                           tile_set, tiles, max_level, w.below, w.inodes, w.ipos, w.tile_off, w.rows, reserved,
+                           FocusSpec{});
         if (scanned)
             hipLaunchKernelGGL(tree_scan_kernel<true>, dim3(kTreeRows, n_sets), dim3(kScanBlock), 0, stream, sets, tiles,
                                w.rows, w.totals);
-        hipLaunchKernelGGL(tree_write_kernel<true>, dim3(tiles), dim3(kWriteBlock), 0, stream, P, one, sets, tile_set,
-                           tiles, max_level, w.inodes, w.ipos, w.tile_off, w.below, w.rows, scanned, w.totals, leaves,
+        hipLaunchKernelGGL((tree_write_kernel<true, false>), dim3(tiles), dim3(kWriteBlock), 0, stream, P, one, sets,
+                           tile_set, tiles, max_level, w.inodes, w.ipos, w.tile_off, w.below, w.rows, scanned, w.totals, leaves,
                            counts, node_keys, child, level_offsets, static_cast<TreeState*>(nullptr),
-                           static_cast<const uint32_t*>(nullptr), static_cast<const uint32_t*>(nullptr), res);
+                           static_cast<const uint32_t*>(nullptr), static_cast<const uint32_t*>(nullptr), res, FocusSpec{});
     }
     if (empty_sets)
         hipLaunchKernelGGL(tree_empty_sets_kernel, dim3((n_sets + 63) / 64), dim3(64), 0, stream, sets, n_sets, leaves,
