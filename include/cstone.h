@@ -335,10 +335,10 @@ CSTONE_API cstone_status cstone_gather_xyz(const double* x, const double* y, con
  * in cstone_rebalance, and so are its errors. Synchronises `stream` once per
  * round. ws: cstone_global_rebalance_workspace_bytes(leaf_capacity, n_shards).
  *
- * cstone_build_sharded: keys of every particle (Sec. 3), every shard sorted
- * on its own (sorted_keys and perm per shard, perm relative to the shard's
- * first particle), then cstone_global_rebalance from `leaves` (e.g. the root
- * {0, 8^L}). ws: cstone_build_sharded_workspace_bytes (0 for bad offsets).
+ * cstone_build_sharded: keys of every particle (Sec. 3), every shard's keys
+ * sorted (sorted_keys and perm per shard, perm relative to the shard's first
+ * particle), and what cstone_global_rebalance makes of `leaves` (e.g. the root
+ * {0, 8^L}), for up to 64 shards out of one sort of all keys. ws: cstone_build_sharded_workspace_bytes (0 for bad offsets).
  * Errors as cstone_build (no linking: cstone_link_octree on the result).
  *
  * cstone_sfc_partition: groups the leaves into n_ranks bins of consecutive
@@ -389,7 +389,9 @@ CSTONE_API cstone_status cstone_sfc_partition(const uint32_t* counts, size_t n_l
  * result is the unique tree in which a node is split iff it holds more than
  * n_crit particles, lies above level L and fails the MAC. Arguments, outputs
  * and errors as cstone_rebalance; theta >= 0 and finite, focus_start <=
- * focus_end <= 8^L. Synchronises `stream` once per round.
+ * focus_end <= 8^L. Synchronises `stream` once; once per round where max_iters
+ * is below L + 1, a round exceeds the capacity or n is above 2^25 (from the root
+ * 2^27).
  * ws: cstone_focus_rebalance_workspace_bytes(leaf_capacity).
  *
  * cstone_focus_mac (f^LE_2): fails[p] = 1 if node p of a linked octree (NK,

@@ -205,6 +205,8 @@ bool tree_possible(size_t n, uint32_t max_iters);
 
 // The whole rebalance loop of one set, and its links (unless node_keys is
 // NULL), enqueued without a host synchronisation.
+// Exclusive scan of each of n_rows rows in place, one block per row; totals: n_rows.
+void launch_row_scan(uint32_t* rows, uint32_t n_rows, uint32_t row_length, uint32_t* totals, hipStream_t stream);
 struct FocusSpec;
 size_t focus_tree_workspace_bytes(size_t n, size_t cap);
 class TreePass {

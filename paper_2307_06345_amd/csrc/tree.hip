@@ -993,6 +993,11 @@ cstone_status TreePass::wait(bool* fits) {
     return CSTONE_OK;
 }
 
+void launch_row_scan(uint32_t* rows, uint32_t n_rows, uint32_t row_length, uint32_t* totals, hipStream_t stream) {
+    const BatchSet* no_sets = nullptr;
+    hipLaunchKernelGGL(tree_scan_kernel<false>, dim3(n_rows), dim3(kScanBlock), 0, stream, no_sets, row_length, rows, totals);
+}
+
 // ---- batched trees -------------------------------------------------------------------
 
 namespace {
