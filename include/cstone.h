@@ -305,7 +305,11 @@ CSTONE_API cstone_status cstone_compact_octree(const uint64_t* leaves, const uin
  * doubles, not aliasing; perm: device, a permutation of 0 .. n-1, e.g. from
  * cstone_sort). cstone_gather_xyz does it for x, y, z: as three passes (one
  * array's reads stay in the last-level cache for n up to 2^25) or, with
- * fused != 0, one pass over all three. Asynchronous. Errors: INVALID_ARG.
+ * fused != 0, one pass over all three. cstone_gather_xyz_packed does the same
+ * with room to put x, y, z side by side first, so that a scattering perm costs
+ * one read per particle, not three; x, y, z hold n doubles each. ws:
+ * cstone_gather_xyz_workspace_bytes(n), 24 B per particle, or 0 where n is too
+ * small to gain (ws may be NULL then). Asynchronous. Errors: INVALID_ARG.
  */
 CSTONE_API size_t cstone_octree_node_counts_workspace_bytes(size_t n_leaves);
 CSTONE_API cstone_status cstone_octree_node_counts(const uint64_t* leaves, const uint32_t* counts, size_t n_leaves,
@@ -316,6 +320,10 @@ CSTONE_API cstone_status cstone_gather(const double* src, const uint32_t* perm, 
 CSTONE_API cstone_status cstone_gather_xyz(const double* x, const double* y, const double* z, const uint32_t* perm,
                                            size_t n, double* ox, double* oy, double* oz, int fused,
                                            hipStream_t stream);
+CSTONE_API size_t cstone_gather_xyz_workspace_bytes(size_t n);
+CSTONE_API cstone_status cstone_gather_xyz_packed(const double* x, const double* y, const double* z,
+                                                  const uint32_t* perm, size_t n, double* ox, double* oy, double* oz,
+                                                  void* ws, size_t ws_bytes, hipStream_t stream);
 
 /* ------------------------------------------------------------------------
  * The replicated tree of particles held by several ranks, and the domain

@@ -99,6 +99,8 @@ def _load() -> ctypes.CDLL:
         "cstone_octree_node_counts": (i32, [P, P, sz, P, sz, P, P, sz, P]),
         "cstone_gather": (i32, [P, P, sz, P, P]),
         "cstone_gather_xyz": (i32, [P, P, P, P, sz, P, P, P, i32, P]),
+        "cstone_gather_xyz_workspace_bytes": (sz, [sz]),
+        "cstone_gather_xyz_packed": (i32, [P, P, P, P, sz, P, P, P, P, sz, P]),
         "cstone_global_rebalance_workspace_bytes": (sz, [sz, u32]),
         "cstone_global_rebalance": (i32, [P, P, u32, u32, P, psz, sz, P, u32, pu32, P, sz, P]),
         "cstone_build_sharded_workspace_bytes": (sz, [P, u32, sz]),
@@ -352,6 +354,25 @@ def gather(src, perm, out=None, stream=None) -> torch.Tensor:
     return out
 
 
+def _pack_scratch(src, out, n: int):
+    """Scratch of the gather's packed route (on the current stream), or None
+    where the separate passes have to do: too few particles, sources that hold
+    more or less than the permutation (a selection of particles), results that
+    share memory with sources (passes go one after another), no memory left."""
+    nbytes = _lib.cstone_gather_xyz_workspace_bytes(n)
+    if nbytes == 0 or any(t.numel() != n for t in src):
+        return None
+    at = [t.data_ptr() for t in src]
+    for o in out:
+        p = o.data_ptr()
+        if any(abs(p - q) < 8 * n for q in at):
+            return None
+    try:
+        return _workspace(nbytes, src[0].device)
+    except torch.OutOfMemoryError:
+        return None
+
+
 def gather_xyz(x, y, z, perm, out=None, fused: bool = False, stream=None):
     """(x, y, z) in curve order: each taken through perm."""
     n = perm.numel()
@@ -359,6 +380,11 @@ def gather_xyz(x, y, z, perm, out=None, fused: bool = False, stream=None):
         _dev(t, torch.float64)
     if out is None:
         out = tuple(torch.empty(n, dtype=torch.float64, device=x.device) for _ in range(3))
+    ws = None if fused or stream is not None else _pack_scratch((x, y, z), out, n)
+    if ws is not None:
+        _check(_lib.cstone_gather_xyz_packed(_ptr(x), _ptr(y), _ptr(z), _ptr(perm), n, *(_ptr(o) for o in out), _ptr(ws),
+                                             ws.numel(), _stream(stream)), "cstone_gather_xyz_packed")
+        return out
     _check(_lib.cstone_gather_xyz(_ptr(x), _ptr(y), _ptr(z), _ptr(perm), n, *(_ptr(o) for o in out), int(fused),
                                   _stream(stream)), "cstone_gather_xyz")
     return out

@@ -150,6 +150,17 @@ cstone_status cstone_gather_xyz(const double* x, const double* y, const double* 
     return launch_gather(src, perm, n, dst, 3, fused != 0, stream);
 }
 
+size_t cstone_gather_xyz_workspace_bytes(size_t n) { return n > kMaxN ? 0 : gather_packed_workspace_bytes(n); }
+
+cstone_status cstone_gather_xyz_packed(const double* x, const double* y, const double* z, const uint32_t* perm, size_t n,
+                                       double* ox, double* oy, double* oz, void* ws, size_t ws_bytes,
+                                       hipStream_t stream) {
+    if (n > kMaxN || (n && (!x || !y || !z || !perm || !ox || !oy || !oz))) return CSTONE_ERR_INVALID_ARG;
+    const double* src[3] = {x, y, z};
+    double* dst[3] = {ox, oy, oz};
+    return launch_gather_packed(src, perm, n, dst, ws, ws_bytes, stream);
+}
+
 size_t cstone_build_workspace_bytes(size_t n, size_t leaf_capacity) {
     Carve c(nullptr);
     c.take<uint64_t>(n);  // unsorted keys

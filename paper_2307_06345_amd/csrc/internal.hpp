@@ -149,6 +149,9 @@ cstone_status launch_octree_node_counts(const uint64_t* leaves, const uint32_t* 
                                         size_t ws_bytes, hipStream_t stream);
 cstone_status launch_gather(const double* const* src, const uint32_t* perm, size_t n, double* const* dst, int arrays,
                             bool fused, hipStream_t stream);
+size_t gather_packed_workspace_bytes(size_t n);  // 0: too few for it
+cstone_status launch_gather_packed(const double* const* src, const uint32_t* perm, size_t n, double* const* dst, void* ws,
+                                   size_t ws_bytes, hipStream_t stream);
 
 // global.hip — the replicated tree of sharded particles, its partition
 size_t global_rebalance_workspace_bytes(size_t leaf_capacity, uint32_t n_shards);

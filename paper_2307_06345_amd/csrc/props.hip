@@ -13,7 +13,10 @@
 // arrays): dst[i] = src[perm[i]]. The writes and the reads of perm stream; the
 // source reads follow the curve, scattered for unsorted input. One array per
 // pass keeps the array being gathered (8 B per particle) resident in the
-// 256 MB last-level cache for inputs up to 2^25 particles.
+// 256 MB last-level cache for inputs up to 2^25 particles. Every scattered read
+// of 8 B moves a whole line all the same, so with room for 24 B per particle the
+// three coordinates are first put side by side and read together (see
+// gather_packed_kernel).
 #include <algorithm>
 
 #include "common.hpp"
@@ -150,6 +153,124 @@ __global__ __launch_bounds__(kGatherBlock) void gather_kernel(const double* __re
     }
 }
 
+constexpr int kPackBlock = 256;
+constexpr uint32_t kPackTile = 1024;  // particles a block packs at a time
+constexpr uint32_t kPackNear = 1u << 15;
+
+// Whether perm scatters: more than a quarter of 64 pairs of neighbours spread
+// over it lie kPackNear (256 KB of an array, which L2 holds many times) or more
+// apart. Random input has nearly all of them apart, input in the order of an
+// earlier step next to none. The same for every wave.
+__device__ __forceinline__ bool perm_scatters(const uint32_t* __restrict__ perm, uint32_t n) {
+    const uint32_t i = lane_id() * (n / kWave);  // i + 1 < n
+    const uint32_t a = perm[i], b = perm[i + 1];
+    return __popcll(__ballot((a > b ? a - b : b - a) >= kPackNear)) * 4 > kWave;
+}
+
+// rec[i] = {x[i], y[i], z[i]}, through LDS so that both sides are whole lines,
+// if perm scatters; *packed says so. Bound: 48 B a particle (2^24: 145 us, 5.5 TB/s).
+__global__ __launch_bounds__(kPackBlock) void gather_pack_kernel(const double* __restrict__ x, const double* __restrict__ y,
+                                                                 const double* __restrict__ z,
+                                                                 const uint32_t* __restrict__ perm, uint32_t n,
+                                                                 double* __restrict__ rec, uint32_t* packed) {
+    __shared__ double t[3 * kPackTile];
+    const bool scatters = perm_scatters(perm, n);
+    if (blockIdx.x == 0 && threadIdx.x == 0) *packed = scatters;
+    if (!scatters) return;
+    const uint32_t tiles = (n - 1) / kPackTile + 1;
+    for (uint32_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+        const size_t base = static_cast<size_t>(tile) * kPackTile;
+        const uint32_t m = static_cast<uint32_t>(min<size_t>(kPackTile, n - base));
+#pragma unroll
+        for (uint32_t k = 0; k < kPackTile / kPackBlock; ++k) {
+            const uint32_t l = k * kPackBlock + threadIdx.x;
+            if (l < m) {
+                t[3 * l] = x[base + l];
+                t[3 * l + 1] = y[base + l];
+                t[3 * l + 2] = z[base + l];
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (uint32_t k = 0; k < 3 * kPackTile / kPackBlock; ++k) {
+            const uint32_t l = k * kPackBlock + threadIdx.x;
+            if (l < 3 * m) rec[3 * base + l] = t[l];
+        }
+        __syncthreads();
+    }
+}
+
+// The gather itself. From the records, the first third of the blocks takes all;
+// where perm does not scatter, the three thirds each take one array, one after
+// another: a pass over one array has a smaller window to keep in the L1 (all
+// three at once were 10% slower for 2^24 particles in order up to 2000 places).
+// Bound: scattered reads, one or two lines per record. 2^24 particles in random
+// order: three passes over the arrays 990 us, records 145 + 385 (32-byte records
+// 175 + 345), 2^22: 226 against 134 us, 2^21: 98 against 67, 2^20: 44 against 34.
+// Particles in order: 2^24 178 against 170 us, 2^22 38 against 39, 2^21 23 against
+// 21, but 2^20 14 against 17 with what the call does on the host, so from 2^21 on.
+// The records' stores go past the caches (2^25: 919 -> 838 us).
+constexpr uint32_t kPackedTile = kGatherBlock * kGatherItems;
+__global__ __launch_bounds__(kGatherBlock) void gather_packed_kernel(const double* __restrict__ x, const double* __restrict__ y,
+                                                                     const double* __restrict__ z,
+                                                                     const double* __restrict__ rec,
+                                                                     const uint32_t* __restrict__ packed,
+                                                                     const uint32_t* __restrict__ perm, uint32_t n,
+                                                                     uint32_t tiles, double* __restrict__ ox,
+                                                                     double* __restrict__ oy, double* __restrict__ oz) {
+    const uint32_t third = blockIdx.x / tiles, tile = blockIdx.x - third * tiles;
+    const bool records = *packed;  // uniform
+    if (records && third) return;
+    const size_t base = static_cast<size_t>(tile) * kPackedTile + threadIdx.x;
+    size_t src[kGatherItems];
+#pragma unroll
+    for (int i = 0; i < kGatherItems; ++i) src[i] = base + i * kGatherBlock < n ? perm[base + i * kGatherBlock] : 0u;
+    if (records) {
+        double a[kGatherItems], b[kGatherItems], c[kGatherItems];
+#pragma unroll
+        for (int i = 0; i < kGatherItems; ++i) {
+            a[i] = rec[3 * src[i]];
+            b[i] = rec[3 * src[i] + 1];
+            c[i] = rec[3 * src[i] + 2];
+        }
+#pragma unroll
+        for (int i = 0; i < kGatherItems; ++i) {
+            const size_t j = base + i * kGatherBlock;
+            if (j < n) {
+                __builtin_nontemporal_store(a[i], ox + j);
+                __builtin_nontemporal_store(b[i], oy + j);
+                __builtin_nontemporal_store(c[i], oz + j);
+            }
+        }
+        return;
+    }
+    const double* from = third == 0 ? x : (third == 1 ? y : z);
+    double* to = third == 0 ? ox : (third == 1 ? oy : oz);
+    double v[kGatherItems];
+#pragma unroll
+    for (int i = 0; i < kGatherItems; ++i) v[i] = from[src[i]];
+#pragma unroll
+    for (int i = 0; i < kGatherItems; ++i)
+        if (base + i * kGatherBlock < n) to[base + i * kGatherBlock] = v[i];
+}
+
+struct PackWs {
+    double* rec;
+    uint32_t* packed;
+    size_t bytes;
+};
+
+PackWs carve_pack(void* ws, size_t n) {
+    Carve c(ws);
+    PackWs w{};
+    w.rec = c.take<double>(3 * n);
+    w.packed = c.take<uint32_t>(1);
+    w.bytes = c.off;
+    return w;
+}
+
+constexpr size_t kPackMin = size_t{1} << 21;
+
 struct ScanWs {
     uint64_t* words;
     uint32_t* counter;
@@ -220,6 +341,22 @@ cstone_status launch_gather(const double* const* src, const uint32_t* perm, size
                                static_cast<const double*>(nullptr), static_cast<const double*>(nullptr), perm, un,
                                dst[a], static_cast<double*>(nullptr), static_cast<double*>(nullptr));
     }
+    CS_HIP(hipGetLastError());
+    return CSTONE_OK;
+}
+
+size_t gather_packed_workspace_bytes(size_t n) { return n < kPackMin ? 0 : carve_pack(nullptr, n).bytes; }
+
+cstone_status launch_gather_packed(const double* const* src, const uint32_t* perm, size_t n, double* const* dst, void* ws,
+                                   size_t ws_bytes, hipStream_t stream) {
+    if (n < kPackMin) return launch_gather(src, perm, n, dst, 3, false, stream);
+    const PackWs w = carve_pack(ws, n);
+    if (!ws || ws_bytes < w.bytes) return CSTONE_ERR_INVALID_ARG;
+    const uint32_t un = static_cast<uint32_t>(n), tiles = static_cast<uint32_t>((n - 1) / kPackedTile + 1);
+    hipLaunchKernelGGL(gather_pack_kernel, dim3(1024), dim3(kPackBlock), 0, stream, src[0], src[1], src[2], perm, un,
+                       w.rec, w.packed);
+    hipLaunchKernelGGL(gather_packed_kernel, dim3(3 * tiles), dim3(kGatherBlock), 0, stream, src[0], src[1], src[2],
+                       w.rec, w.packed, perm, un, tiles, dst[0], dst[1], dst[2]);
     CS_HIP(hipGetLastError());
     return CSTONE_OK;
 }
