@@ -139,7 +139,7 @@ cstone_status launch_sort_segmented(const uint64_t* keys_in, uint64_t* keys_out,
 // particle arrays by the sort permutation (separate passes, or one fused pass
 // over three arrays)
 // exclusive prefix sum: out[i] = in[0] + ... + in[i - 1] for i <= n (out[n]
-// the total, modulo 2^32), one pass; n < 2^32 - 1
+// the total, modulo 2^32); n < 2^32 - 1
 size_t scan_u32_workspace_bytes(size_t n);
 cstone_status launch_scan_u32(const uint32_t* in, size_t n, uint32_t* out, void* ws, size_t ws_bytes,
                               hipStream_t stream);

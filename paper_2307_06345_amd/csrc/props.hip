@@ -32,51 +32,55 @@ constexpr int kNodeBlock = 256;
 constexpr int kGatherBlock = 256;
 constexpr int kGatherItems = 8;
 
-// Clears the scan's look-back words, its tile counter and its error word.
-__global__ __launch_bounds__(256) void props_setup_kernel(uint64_t* words, size_t n_words, uint32_t* counter,
-                                                          uint32_t* err) {
-    const size_t stride = static_cast<size_t>(gridDim.x) * blockDim.x;
-    for (size_t i = static_cast<size_t>(blockIdx.x) * blockDim.x + threadIdx.x; i < n_words; i += stride) words[i] = 0;
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        *counter = 0;
-        *err = 0;
-    }
-}
+// Exclusive prefix sum in two launches: the tiles' sums, then every tile its
+// part, after the sums of the tiles before it, which its block adds up itself
+// (one read per 256 tiles, all in flight). Above kSumTiles tiles a launch between
+// the two scans the sums. Tiles wait for nobody: a decoupled look-back, at 33 ns
+// per tile of polling across the XCDs, took 20 us for 1.1 M counts, now 13.
+constexpr uint32_t kSumTiles = 2048;
 
-// S[i] = counts[0] + ... + counts[i - 1] for i <= nl (S[nl] the total): one
-// pass, tiles taken in order from a counter, decoupled look-back across tiles.
-__global__ __launch_bounds__(kScanBlock) void exclusive_scan_kernel(const uint32_t* __restrict__ counts, uint32_t nl,
-                                                                    uint32_t* __restrict__ S, uint64_t* words,
-                                                                    uint32_t* counter, uint32_t* err) {
-    __shared__ uint32_t slot;
-    __shared__ uint64_t scan_tmp[kScanBlock / kWave];
-    __shared__ uint64_t tile_prefix;
-    const uint32_t tile = take_tile(counter, &slot);
-    const uint32_t base = tile * kScanTile + threadIdx.x * kScanItems;  // blocked: each thread a run of items
-    uint32_t v[kScanItems];
-    uint64_t mine = 0;
+__device__ __forceinline__ uint32_t scan_tile_load(const uint32_t* __restrict__ counts, uint32_t n, uint64_t base,
+                                                   uint32_t v[kScanItems]) {
+    uint32_t mine = 0;
 #pragma unroll
-    for (int i = 0; i < kScanItems; ++i) {
-        v[i] = base + i < nl ? counts[base + i] : 0u;
+    for (int i = 0; i < kScanItems; ++i) {  // blocked: each thread a run of items
+        v[i] = base + i < n ? counts[base + i] : 0u;
         mine += v[i];
     }
-    uint64_t total;
-    const uint64_t excl = block_exclusive_sum<uint64_t, kScanBlock>(mine, scan_tmp, &total);
-    if (threadIdx.x < kWave) {  // the first wave publishes the aggregate and resolves the prefix
-        const uint32_t lane = lane_id();
-        if (lane == 0) st_agent(words + tile, lb_word(tile == 0 ? kFlagInc : kFlagAgg, 1, total));
-        uint64_t prefix = 0;
-        if (tile > 0) {
-            prefix = lookback_wave<4>(words, tile, 1, err);
-            if (lane == 0) st_agent(words + tile, lb_word(kFlagInc, 1, prefix + total));
+    return mine;
+}
+
+__global__ __launch_bounds__(kScanBlock) void scan_sums_kernel(const uint32_t* __restrict__ counts, uint32_t n,
+                                                               uint32_t* __restrict__ sums) {
+    __shared__ uint32_t tmp[kScanBlock / kWave];
+    uint32_t v[kScanItems], total;
+    const uint64_t base = static_cast<uint64_t>(blockIdx.x) * kScanTile + threadIdx.x * kScanItems;
+    (void)block_exclusive_sum<uint32_t, kScanBlock>(scan_tile_load(counts, n, base, v), tmp, &total);
+    if (threadIdx.x == 0) sums[blockIdx.x] = total;
+}
+
+// sums: the tiles' sums, or scanned, the sums of all tiles before each.
+__global__ __launch_bounds__(kScanBlock) void exclusive_scan_kernel(const uint32_t* __restrict__ counts, uint32_t n,
+                                                                    const uint32_t* __restrict__ sums, bool scanned,
+                                                                    uint32_t* __restrict__ S) {
+    __shared__ uint32_t tmp[kScanBlock / kWave];
+    uint32_t v[kScanItems], total, prefix = 0;
+    const uint64_t base = static_cast<uint64_t>(blockIdx.x) * kScanTile + threadIdx.x * kScanItems;
+    if (scanned) {
+        prefix = sums[blockIdx.x];
+    } else {
+        uint32_t before = 0;
+#pragma unroll
+        for (uint32_t k = 0; k < kSumTiles / kScanBlock; ++k) {
+            const uint32_t t = k * kScanBlock + threadIdx.x;
+            before += t < blockIdx.x ? sums[t] : 0u;
         }
-        if (lane == 0) tile_prefix = prefix;
+        (void)block_exclusive_sum<uint32_t, kScanBlock>(before, tmp, &prefix);
     }
-    __syncthreads();
-    uint64_t run = tile_prefix + excl;
+    uint32_t run = prefix + block_exclusive_sum<uint32_t, kScanBlock>(scan_tile_load(counts, n, base, v), tmp, &total);
 #pragma unroll
     for (int i = 0; i < kScanItems; ++i) {
-        if (base + i <= nl) S[base + i] = static_cast<uint32_t>(run);  // the entry at nl is the total
+        if (base + i <= n) S[base + i] = run;  // the entry at n is the total
         run += v[i];
     }
 }
@@ -272,9 +276,7 @@ PackWs carve_pack(void* ws, size_t n) {
 constexpr size_t kPackMin = size_t{1} << 21;
 
 struct ScanWs {
-    uint64_t* words;
-    uint32_t* counter;
-    uint32_t* err;
+    uint32_t *sums, *total;
     size_t tiles, bytes;
 };
 
@@ -282,9 +284,8 @@ ScanWs carve_scan(void* ws, size_t n) {
     Carve c(ws);
     ScanWs w{};
     w.tiles = (n + 1 + kScanTile - 1) / kScanTile;
-    w.words = c.take<uint64_t>(w.tiles);
-    w.counter = c.take<uint32_t>(1);
-    w.err = c.take<uint32_t>(1);
+    w.sums = c.take<uint32_t>(w.tiles);
+    w.total = c.take<uint32_t>(1);
     w.bytes = c.off;
     return w;
 }
@@ -297,10 +298,12 @@ cstone_status launch_scan_u32(const uint32_t* in, size_t n, uint32_t* out, void*
                               hipStream_t stream) {
     ScanWs w = carve_scan(ws, n);
     if (ws_bytes < w.bytes || n >= 0xffffffffull) return CSTONE_ERR_INVALID_ARG;
-    hipLaunchKernelGGL(props_setup_kernel, dim3(static_cast<uint32_t>(std::min<size_t>((w.tiles + 255) / 256, 256))),
-                       dim3(256), 0, stream, w.words, w.tiles, w.counter, w.err);
-    hipLaunchKernelGGL(exclusive_scan_kernel, dim3(static_cast<uint32_t>(w.tiles)), dim3(kScanBlock), 0, stream, in,
-                       static_cast<uint32_t>(n), out, w.words, w.counter, w.err);
+    const uint32_t un = static_cast<uint32_t>(n), tiles = static_cast<uint32_t>(w.tiles);
+    const bool scanned = tiles > kSumTiles;
+    if (tiles > 1)
+        hipLaunchKernelGGL(scan_sums_kernel, dim3(tiles), dim3(kScanBlock), 0, stream, in, un, w.sums);
+    if (scanned) launch_row_scan(w.sums, 1, tiles, w.total, stream);
+    hipLaunchKernelGGL(exclusive_scan_kernel, dim3(tiles), dim3(kScanBlock), 0, stream, in, un, w.sums, scanned, out);
     CS_HIP(hipGetLastError());
     return CSTONE_OK;
 }
