@@ -66,7 +66,10 @@ def path_bytes(model: dict, n: int) -> dict:
     first top pass (its histogram comes with the keys, its values are the
     indices), 24 N for each of the two later top passes, 8 N for the bucket
     pass (every key read once; keys that move are data-dependent and not
-    counted), and nothing for the low passes when no bucket is listed."""
+    counted, nor is the 24 N pass that crowded keys take before the others), and nothing for the low passes when no bucket is listed. (The
+    tree and its links are written straight from the sorted keys: 9 N and 24 B
+    a leaf, less than the model's rounds and link, which stay so that figures
+    compare.)"""
     sort = 20 * n + 2 * 24 * n + 8 * n
     out = dict(model)
     out["sort"] = sort
@@ -238,8 +241,8 @@ def bench_beyond(b, x, y, z, s, r, reps: int) -> dict:
         or one fused pass);
       the link through the binary radix tree against the default link;
       the compact octree (empty buckets removed);
-      the sharded build with 8 shards (keys, 8 shard sorts, rounds with summed
-        counts and a host synchronisation each) against the plain build;
+      the sharded build with 8 shards (one sort of all keys, parted into the
+        shards, the tree from it) against the plain build;
       the tree focused on 1/64 of the curve, theta 0.5, from the root."""
     import torch
 
@@ -595,7 +598,7 @@ def main():
                    "rounds": r.rounds, "leaves_per_round": leaves_hist},
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS, "traffic": traffic,
-                     "kernel": "onesweep_kernel<false,true> (top digit passes 2 and 3 of the split particle sort)",
+                     "kernel": "onesweep_kernel (top digit passes 2 and 3 of the split particle sort)",
                      "bytes_per_launch": pass_bytes, "avg_launch_ms": pass_ms,
                      "kernel_source_digest": digest},
         "build": {"stage_ms": {"keys": stage[0], "sort": stage[1], "rebalance": stage[2], "link": stage[3]},

@@ -428,7 +428,8 @@ __device__ __forceinline__ void shard_smem_fill(const uint64_t* off, uint32_t G,
     __syncthreads();
 }
 
-// rows[g][tile]: particles of shard g among the tile's. Bound: reading perm, 4 B a particle.
+// rows[g][tile]: particles of shard g among the tile's. Bound: the chain of
+// search, ballots and counts per item (33 us for 2^24; reading perm alone is 13).
 __global__ __launch_bounds__(kShardBlock) void shard_tile_counts_kernel(const uint32_t* __restrict__ perm, uint64_t n,
                                                                         const uint64_t* __restrict__ off, uint32_t G,
                                                                         uint32_t bits, uint32_t* __restrict__ rows) {
@@ -454,7 +455,8 @@ __global__ __launch_bounds__(kShardBlock) void shard_tile_counts_kernel(const ui
 
 // The tile's keys and particles to their shards, in order; rows scanned. They
 // are put in the shards' order in LDS first, so that every shard's run is
-// written whole. Bound: 12 B a particle read and 12 written.
+// written whole. Bound: 12 B a particle read and 12 written (90 us for 2^24, 4.5
+// TB/s).
 __global__ __launch_bounds__(kShardBlock) void shard_write_kernel(const uint64_t* __restrict__ P,
                                                                   const uint32_t* __restrict__ perm, uint64_t n,
                                                                   const uint64_t* __restrict__ off, uint32_t G,
