@@ -790,10 +790,16 @@ __global__ __launch_bounds__(64) void tree_empty_sets_kernel(const BatchSet* __r
 // splits one level a round, a subtree under a leaf of the tree merges one
 // level a round), and no round's array is longer than the leaves of the two
 // arrays that lie on their finer side together (`inter`).
+//
+// Bound: the chain of reads and searches of a tile, one after another, so as
+// many blocks as fit: two arrays of 28 M leaves 397 us with four on a CU, 308
+// with six (reading both is 90). Starting each search where the block's tile
+// before ended gains 9 us more, not worth its code.
 
 constexpr int kCmpBlock = 256;
 constexpr uint32_t kCmpTile = 1024;
 constexpr uint32_t kCmpOld = 2048;
+constexpr size_t kCmpBlocks = 6 * 256;  // as many as the LDS of all CUs holds at once
 
 __device__ __forceinline__ int delta_level(uint64_t delta) { return kL - (63 - clz64(delta)) / 3; }
 
@@ -970,7 +976,7 @@ bool TreePass::run(const uint64_t* P, size_t n, uint32_t n_crit, uint64_t* leave
                        w.inodes, w.ipos, w.tile_off, w.below, w.rows, scanned, w.totals, K, counts, node_keys, child,
                        level_offsets, st_, input_flags, listed, TreeResults{}, spec);
     if (incremental_) {
-        const uint32_t grid = static_cast<uint32_t>(std::min<size_t>((cap + kCmpTile - 1) / kCmpTile, 1024));
+        const uint32_t grid = static_cast<uint32_t>(std::min<size_t>((cap + kCmpTile - 1) / kCmpTile, kCmpBlocks));
         hipLaunchKernelGGL(tree_compare_kernel, dim3(grid), dim3(kCmpBlock), 0, stream, leaves,
                            static_cast<uint32_t>(nl0), w.K_new, static_cast<uint64_t>(cap), st_);
         hipLaunchKernelGGL(tree_commit_kernel, dim3(static_cast<uint32_t>(std::min<size_t>((cap + 256) / 256, 2048))),
