@@ -223,7 +223,7 @@ public:
              const FocusSpec* focus = nullptr);
     // focus: the tree focused on its range (node_keys NULL); ws: focus_tree_workspace_bytes.
     // listed: NULL, or the word that says whether the keys' sort is incomplete
-    // (see sort_listed_word); `leaves` is then left alone unless from the root.
+    // (see sort_listed_word); if it is, no tree is written and `leaves` is left alone.
     // Synchronises. *fits false: the tree or a round on the way to it exceeds
     // the capacity; `leaves` holds the start array unless that was the root,
     // and the rounds have to say how far they come.

@@ -39,6 +39,7 @@
 #include "common.hpp"
 #include "focus.hpp"
 #include "internal.hpp"
+#include "overlap.hpp"
 
 namespace cs {
 namespace {
@@ -494,6 +495,9 @@ __global__ __launch_bounds__(kWriteBlock) void tree_write_kernel(const uint64_t*
     }
     uint64_t* Ko = K + o.leaf_off;
     uint32_t* Co = counts ? counts + o.leaf_off : nullptr;
+    // Of keys that the sort has not finished only the state is written, to say so:
+    // the tree would be thrown away, and what it leaves out is not there to read.
+    const uint32_t unsorted = listed ? *listed : 0u;
     const bool fits = nl <= o.cap;
     if (tile == 0) {
         if constexpr (BATCH) {
@@ -504,10 +508,10 @@ __global__ __launch_bounds__(kWriteBlock) void tree_write_kernel(const uint64_t*
                 st->n_leaves = nl;
                 st->depth = depth;
                 st->input_flags = input_flags ? *input_flags : 0u;
-                st->listed = listed ? *listed : 0u;
+                st->listed = unsorted;
             }
         }
-        if (fits) {
+        if (fits && !unsorted) {
             if (tid == 0) {
                 Ko[nl] = kKeyEnd;
                 if (ni == 0) {  // the root alone
@@ -522,7 +526,7 @@ __global__ __launch_bounds__(kWriteBlock) void tree_write_kernel(const uint64_t*
             if (nk && tid <= static_cast<uint32_t>(kL + 1)) lo_out[static_cast<size_t>(s) * (kL + 2) + tid] = lo;
         }
     }
-    if (!fits) return;
+    if (!fits || unsorted) return;
     const uint32_t N = o.n_crit, n = o.n;
     const uint64_t* Ps = P + o.first;
     const uint32_t p0 = before[kTreeLevels];
@@ -803,20 +807,6 @@ constexpr size_t kCmpBlocks = 6 * 256;  // as many as the LDS of all CUs holds a
 
 __device__ __forceinline__ int delta_level(uint64_t delta) { return kL - (63 - clz64(delta)) / 3; }
 
-// Last index in [lo, hi) of a sorted array whose key is <= k (lo if none).
-template <class A>
-__device__ __forceinline__ uint32_t at_or_before(const A& a, uint32_t lo, uint32_t hi, uint64_t k) {
-    const uint32_t first = lo;
-    while (lo < hi) {
-        const uint32_t mid = lo + ((hi - lo) >> 1);
-        if (a[mid] <= k)
-            lo = mid + 1;
-        else
-            hi = mid;
-    }
-    return lo > first ? lo - 1 : first;
-}
-
 __global__ __launch_bounds__(kCmpBlock) void tree_compare_kernel(const uint64_t* __restrict__ K_old, uint32_t nl_old,
                                                                  const uint64_t* __restrict__ K, uint64_t cap,
                                                                  TreeState* st) {
@@ -825,7 +815,7 @@ __global__ __launch_bounds__(kCmpBlock) void tree_compare_kernel(const uint64_t*
     __shared__ uint32_t range[2];
     __shared__ uint32_t red_n[kCmpBlock / kWave], red_d[kCmpBlock / kWave];
     const uint64_t nl = st->n_leaves;
-    if (nl > cap) return;
+    if (nl > cap || st->listed) return;  // (nothing was written)
     const uint32_t tiles = static_cast<uint32_t>((nl + kCmpTile - 1) / kCmpTile);
     const uint32_t tid = threadIdx.x;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(tid / kWave);
@@ -842,15 +832,16 @@ __global__ __launch_bounds__(kCmpBlock) void tree_compare_kernel(const uint64_t*
         }
         __syncthreads();
         const uint32_t p0 = range[0], p1 = range[1];
-        const uint32_t q0 = p0 ? p0 - 1 : 0;  // the old leaf around the tile's first key
-        const uint32_t held = p1 - q0 + 1;    // old keys q0 .. p1 (p1 <= nl_old: K_old has a closing key)
+        const OldKeys old = old_keys(p0, p1);  // (at most nl_old: K_old has a closing key)
+        const uint32_t q0 = old.first, q1 = old.last;
+        const uint32_t held = q1 - q0 + 1;
         const bool staged = held <= kCmpOld + 2;
         if (staged) {
             for (uint32_t i = tid; i < held; i += kCmpBlock) b[i] = K_old[q0 + i];
             __syncthreads();
         }
         for (uint32_t j = tid; j < m; j += kCmpBlock) {  // leaves as fine as the old one around them, or finer
-            const uint32_t p = staged ? at_or_before(b, 0u, p1 - q0, a[j]) : at_or_before(K_old, q0, p1, a[j]);
+            const uint32_t p = staged ? at_or_before(b, 0u, q1 - q0, a[j]) : at_or_before(K_old, q0, q1, a[j]);
             const uint64_t d_old = staged ? b[p + 1] - b[p] : K_old[p + 1] - K_old[p];
             const int d = delta_level(a[j + 1] - a[j]) - delta_level(d_old);
             if (d >= 0) {
