@@ -13,6 +13,7 @@
 #include <algorithm>
 
 #include "common.hpp"
+#include "depth.hpp"
 #include "internal.hpp"
 
 namespace cs {
@@ -39,69 +40,50 @@ __global__ __launch_bounds__(256) void sort_init_kernel(uint32_t* ghist, size_t 
     }
 }
 
-// ---- depth of the split -------------------------------------------------------
+// ---- depth of the split (see depth.hpp) -----------------------------------------
 //
-// The split sort's three top digits leave buckets of one 27-bit prefix. Where
-// many keys share theirs with hundreds of others (a cluster's core), the bucket
-// kernel and the low passes over listed buckets cost more than one more digit
-// pass below the top ones, after which the buckets are those of one 36-bit
-// prefix. The size of the bucket that a key finds itself in, on average over
-// the keys, tells: n times the share of pairs of keys with one prefix, which a
-// sample of kDeepSample keys estimates (drawn at scattered places: keys in
-// curve order would hide it from an even stride). One block counts the pairs in
-// a hash table in LDS and sets the word that the passes read; nothing returns
-// to the host.
-constexpr uint32_t kDeepSample = 2048;
+// One block counts the sample's pairs in a hash table in LDS and sets the word
+// that the passes read; nothing returns to the host.
 constexpr uint32_t kDeepSlots = 4096;  // twice the sample
-// Mean bucket from which the extra digit pays. Sorts of Plummer keys, three top
-// digits against four: 2^18 keys (mean 6.5) 101 / 109 us, 2^20 (23) 154 / 136,
-// 2^22 (89) 255 / 207, 2^24 (354) 742 / 581, 2^27 (2828) 6149 / 3985; uniform
-// 2^24 (1.1) 468 / 568.
-constexpr uint32_t kDeepBucket = 16;
-constexpr uint32_t kDeepPairs = 4;  // fewer pairs in the sample may be chance
-constexpr uint32_t kDeepMinKeys = 1u << 20;  // shorter sorts gain less than the extra launch costs where it is left out
 
-// All THREADS threads of the block; slots, pairs: LDS.
+struct DepthSmem {
+    uint64_t slots[kDeepSlots];
+    uint64_t sums;  // three counts of 21 bits: pairs, those with the first key, those of them that stay together
+};
+
+// All THREADS threads of the block.
 template <uint32_t THREADS>
-__device__ __forceinline__ void decide_depth(const uint64_t* __restrict__ keys, uint32_t n, uint32_t* slots,
-                                             uint32_t* pairs, uint32_t* deep) {
+__device__ __forceinline__ void decide_depth(const uint64_t* __restrict__ keys, uint32_t n, DepthSmem& sm, uint32_t* deep) {
     constexpr uint32_t kEach = kDeepSample / THREADS;
-    // one place in each of kDeepSample equal shares of the keys, scattered
-    // within it by a multiplicative hash of the share's number; all in flight
     uint64_t key[kEach];
 #pragma unroll
-    for (uint32_t q = 0; q < kEach; ++q) {
-        const uint32_t i = q * THREADS + threadIdx.x;
-        const uint64_t a = static_cast<uint64_t>(n) * i / kDeepSample;
-        const uint64_t len = static_cast<uint64_t>(n) * (i + 1) / kDeepSample - a;
-        key[q] = keys[a + ((static_cast<uint64_t>(i * 2654435761u) * len) >> 32)];
-    }
-    for (uint32_t i = threadIdx.x; i < kDeepSlots; i += THREADS) slots[i] = 0;
-    if (threadIdx.x == 0) *pairs = 0;
+    for (uint32_t q = 0; q < kEach; ++q) key[q] = keys[depth_place(q * THREADS + threadIdx.x, n)];  // all in flight
+    for (uint32_t i = threadIdx.x; i < kDeepSlots; i += THREADS) sm.slots[i] = 0;
+    if (threadIdx.x == 0) sm.sums = 0;
     __syncthreads();
-    uint32_t mine = 0;
+    uint64_t mine = 0;
+    static_assert(kDeepSample * kDepthCount < 1u << 21, "the counts' bits");
 #pragma unroll
     for (uint32_t q = 0; q < kEach; ++q) {
-        // word: prefix + 1 (0 is free) << 4, and the keys seen with it, counted up to 15
-        const uint32_t tag = (static_cast<uint32_t>(key[q] >> 36) + 1u) << 4;
-        for (uint32_t s = (tag * 2654435761u) >> 20;; s = (s + 1) & (kDeepSlots - 1)) {  // the table is half empty
-            const uint32_t old = atomicCAS(&slots[s], 0u, tag | 1u);
+        const uint64_t word = depth_word(key[q]);
+        // (the table is half empty)
+        for (uint32_t s = (static_cast<uint32_t>(word >> 32) * 2654435761u) >> 20;; s = (s + 1) & (kDeepSlots - 1)) {
+            const uint64_t old = atomicCAS(reinterpret_cast<unsigned long long*>(&sm.slots[s]), 0ull, word | 1u);
             if (old == 0) break;
-            if ((old & ~15u) == tag) {
-                const uint32_t seen = old & 15u;
-                mine += seen;
-                if (seen < 15u) atomicCAS(&slots[s], old, old + 1u);
+            if (depth_one_prefix(old, word)) {
+                const uint64_t seen = old & kDepthCount;
+                mine += seen | 1ull << 21 | (depth_one_digit(old, word) ? 1ull << 42 : 0ull);
+                if (seen < kDepthCount) atomicCAS(reinterpret_cast<unsigned long long*>(&sm.slots[s]), old, old + 1);
                 break;
             }
         }
     }
-    atomicAdd(pairs, mine);
+    mine = wave_sum<uint64_t>(mine);
+    if (lane_id() == 0) atomicAdd(reinterpret_cast<unsigned long long*>(&sm.sums), static_cast<unsigned long long>(mine));
     __syncthreads();
+    constexpr uint64_t kCount = (1u << 21) - 1;
     if (threadIdx.x == 0)
-        *deep = *pairs >= kDeepPairs &&
-                        2ull * *pairs * n >= static_cast<uint64_t>(kDeepBucket) * kDeepSample * kDeepSample
-                    ? 1u
-                    : 0u;
+        *deep = depth_pays(sm.sums & kCount, (sm.sums >> 21) & kCount, sm.sums >> 42, n) ? 1u : 0u;
 }
 
 // Set-up of a build's sort from the key kernel's per-block parts (rows of
@@ -123,9 +105,9 @@ __global__ __launch_bounds__(kKeyBlocksMax) void sort_setup_kernel(uint32_t* ghi
                                                                   uint32_t* flag, uint64_t* clear,
                                                                   size_t clear_words, const uint64_t* __restrict__ keys,
                                                                   uint32_t n, uint32_t* deep) {
-    __shared__ uint32_t red[kDeepSlots];
-    __shared__ uint32_t pairs;
-    static_assert(kKeyBlocksMax <= kDeepSlots, "shared by the sums and the depth's table");
+    __shared__ DepthSmem depth;
+    uint32_t* const red = reinterpret_cast<uint32_t*>(depth.slots);  // (the sums' blocks and the depth's are others)
+    static_assert(kKeyBlocksMax <= 2 * kDeepSlots, "shared by the sums and the depth's table");
     const uint32_t tid = threadIdx.x;
     const size_t t = static_cast<size_t>(blockIdx.x) * blockDim.x + tid;
     const size_t stride = static_cast<size_t>(gridDim.x) * blockDim.x;
@@ -169,7 +151,7 @@ __global__ __launch_bounds__(kKeyBlocksMax) void sort_setup_kernel(uint32_t* ghi
         }
     } else if (j == sums + 1 && deep) {  // block-uniform: the split's depth
         if (n >= kDeepMinKeys)
-            decide_depth<kKeyBlocksMax>(keys, n, red, &pairs, deep);
+            decide_depth<kKeyBlocksMax>(keys, n, depth, deep);
         else if (tid == 0)
             *deep = 0;
     }
@@ -182,13 +164,13 @@ __global__ __launch_bounds__(kKeyBlocksMax) void sort_setup_kernel(uint32_t* ghi
 __global__ __launch_bounds__(kHistBlock) void sort_hist0_kernel(const uint64_t* __restrict__ keys, uint32_t n,
                                                                  uint32_t shift, uint32_t mask, uint32_t bits,
                                                                  uint32_t* __restrict__ ghist, uint32_t* deep) {
-    __shared__ uint32_t h[kDeepSlots];
-    __shared__ uint32_t pairs;
-    static_assert(2 * kMaxRadix <= kDeepSlots, "shared by the counts and the depth's table");
+    __shared__ DepthSmem depth;
+    uint32_t* const h = reinterpret_cast<uint32_t*>(depth.slots);
+    static_assert(kMaxRadix <= kDeepSlots, "shared by the counts and the depth's table");
     const uint32_t blocks = deep ? gridDim.x - 1 : gridDim.x;
     if (blockIdx.x == blocks) {  // block-uniform
         if (n >= kDeepMinKeys)
-            decide_depth<kHistBlock>(keys, n, h, &pairs, deep);
+            decide_depth<kHistBlock>(keys, n, depth, deep);
         return;  // (the word is cleared)
     }
     const uint32_t words = deep ? 2 * kMaxRadix : kMaxRadix;
