@@ -48,6 +48,7 @@ constexpr int kMarkBlock = 512;
 constexpr int kMarkItems = 8;
 constexpr uint32_t kTreeTile = kMarkBlock * kMarkItems;  // particles per tile of all three launches
 constexpr int kMarkWaves = kMarkBlock / kWave;
+constexpr uint32_t kByteMaxCrit = 256;  // N_crit up to which the write launch goes by the particles' bytes
 constexpr size_t kBytesPad = 192;  // a byte after the last particle's, and what the last groups read past it
 
 // Leading octal digits two keys share, 0 .. 21. Keys are below 2^63, so the bits
@@ -137,11 +138,18 @@ struct MarkSmem {
 // cache lines, or the next one's, for N_crit in the hundreds), about 40
 // instructions a key. A wave takes 512 consecutive particles, so that their
 // starts (one particle in 100 at N_crit 64) are gathered in order by ballots
-// without a barrier; only they are expanded.
+// without a barrier; only they are expanded. From N_crit 512 on most waves look
+// at three keys instead (2^27 keys: 305 us for any N_crit before, 160 at 2000 and
+// 64 at 10^6).
 // One wave's 512 particles from place wbase of the tile on: their bytes, and
 // the list of those that start internal nodes (in order; returns how many).
 // FULL: every key that is read exists; otherwise keys past the end read the
-// last key and are masked. BYTES: the particles' bytes are kept.
+// last key and are masked. BYTES: the particles' bytes are kept. Where they are
+// not, and N spans the wave's particles, most waves need not read them: with g
+// the digits that all keys from the one before the first to the last share, and h
+// those of the last and P[first + N], every particle j of the wave has
+// common(P[j - 1], P[j]) >= g and common(P[j], P[j + N]) <= h, so none starts an
+// internal node unless h > g.
 template <bool FULL, bool BYTES>
 __device__ __forceinline__ uint32_t mark_wave(const uint64_t* __restrict__ Ps, uint32_t base, uint32_t wbase, uint32_t n,
                                               uint32_t N, uint32_t max_level, uint8_t* __restrict__ below,
@@ -150,6 +158,13 @@ __device__ __forceinline__ uint32_t mark_wave(const uint64_t* __restrict__ Ps, u
     const uint32_t first = base + wbase;  // wave-uniform
     if (!FULL && first >= n) return 0;
     const uint64_t last = n - 1;
+    if constexpr (!BYTES) {
+        if (static_cast<uint64_t>(first) + N >= n) return 0;
+        if (first && N >= kMarkItems * kWave) {
+            const uint64_t end = Ps[first + kMarkItems * kWave - 1];
+            if (min(common_digits(end, Ps[first + N]), max_level) <= common_digits(Ps[first - 1], end)) return 0;
+        }
+    }
     uint64_t edge = Ps[first ? first - 1 : 0];
     uint64_t a[kMarkItems], b[kMarkItems];
     const uint64_t* pa = Ps + first + lane;
@@ -226,11 +241,21 @@ __global__ __launch_bounds__(kMarkBlock) void tree_mark_kernel(const uint64_t* _
     const uint32_t base = tile * kTreeTile;
     const uint32_t wbase = wave * kMarkItems * kWave;  // the wave's first place
     if (tid < kTreeLevels) sm.level[tid] = 0;
-    if (!FOCUS && tid == 0 && gtile + 1 == n_tiles) below[n] = 0;
+    if (!FOCUS && tid == 0) {  // where a set ends, for those that go by their bytes
+        if (tile == 0) below[0] = 0;
+        if (gtile + 1 == n_tiles) below[n] = 0;
+    }
     const bool full = static_cast<uint64_t>(base) + kTreeTile + N <= n;  // block-uniform: every key exists
     uint32_t* mylist = sm.list + wbase;
-    const uint32_t starts = full ? mark_wave<true, !FOCUS>(Ps, base, wbase, n, N, max_level, below, mylist)
-                                 : mark_wave<false, !FOCUS>(Ps, base, wbase, n, N, max_level, below, mylist);
+    const auto wave_starts = [&](auto bytes) {
+        return full ? mark_wave<true, bytes.value>(Ps, base, wbase, n, N, max_level, below, mylist)
+                    : mark_wave<false, bytes.value>(Ps, base, wbase, n, N, max_level, below, mylist);
+    };
+    uint32_t starts;
+    if constexpr (FOCUS)
+        starts = wave_starts(std::false_type{});
+    else
+        starts = N <= kByteMaxCrit ? wave_starts(std::true_type{}) : wave_starts(std::false_type{});
     if constexpr (FOCUS) {
         if (__syncthreads_or(static_cast<int>(starts))) {  // block-uniform; sm.level is cleared
             focus_fill(focus, fsm);
@@ -408,7 +433,6 @@ constexpr int kWriteWaves = kWriteBlock / kWave;
 // Bound: instructions (about 40 per node for the bytes, its lanes together),
 // and three dependent reads (list, bytes, keys of the children's starts); 24 B
 // of K, counts, NK and CO are written per leaf.
-constexpr uint32_t kByteMaxCrit = 256;  // above it the bytes of 8 N particles are too many round trips: all search
 template <bool BATCH, bool FOCUS>
 __global__ __launch_bounds__(kWriteBlock) void tree_write_kernel(const uint64_t* __restrict__ P, TreeOne one,
                                                                  const BatchSet* __restrict__ sets,
@@ -960,9 +984,7 @@ bool TreePass::run(const uint64_t* P, size_t n, uint32_t n_crit, uint64_t* leave
     const FocusSpec spec = focus ? *focus : FocusSpec{};
     hipLaunchKernelGGL(mark, dim3(tiles), dim3(kMarkBlock), 0, stream, P, one, no_sets, no_table, tiles, max_level,
                        w.below, w.inodes, w.ipos, w.tile_off, w.rows, &st_->reserved, spec);
-    if (scanned)
-        hipLaunchKernelGGL(tree_scan_kernel<false>, dim3(kTreeRows), dim3(kScanBlock), 0, stream, no_sets, tiles, w.rows,
-                           w.totals);
+    if (scanned) launch_row_scan(w.rows, kTreeRows, tiles, w.totals, stream);
     hipLaunchKernelGGL(write, dim3(tiles), dim3(kWriteBlock), 0, stream, P, one, no_sets, no_table, tiles, max_level,
                        w.inodes, w.ipos, w.tile_off, w.below, w.rows, scanned, w.totals, K, counts, node_keys, child,
                        level_offsets, st_, input_flags, listed, TreeResults{}, spec);
