@@ -398,7 +398,7 @@ CSTONE_API cstone_status cstone_sfc_partition(const uint32_t* counts, size_t n_l
  * n_crit particles, lies above level L and fails the MAC. Arguments, outputs
  * and errors as cstone_rebalance; theta >= 0 and finite, focus_start <=
  * focus_end <= 8^L. Synchronises `stream` once; once per round where max_iters
- * is below L + 1, a round exceeds the capacity or n is above 2^25 (from the root
+ * is below L + 1, a round exceeds the capacity or n is above 2^21 (from the root
  * 2^27).
  * ws: cstone_focus_rebalance_workspace_bytes(leaf_capacity).
  *

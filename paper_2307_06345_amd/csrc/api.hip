@@ -21,6 +21,16 @@ constexpr size_t kMaxN = 0xffffffffull;  // counts, perm, CO and LO are uint32
 
 constexpr size_t kListMaxKeys = size_t{1} << 25;
 
+// Whether a build takes its tree from the sorted keys directly, where it may. Only
+// large builds from an array of few leaves are faster by rounds, which go by the
+// leaves and not by the keys. Builds from the last step's tree, direct against
+// rounds in us, uniform keys: 2^26, N_crit 64 (a leaf per 32 keys) 2321 / 2277,
+// N_crit 256 2318 / 2232, 1000 2202 / 2117; 2^25 1246 / 1265, 1182 / 1128, 1161 /
+// 1148; Plummer 2^27, N_crit 64 (a leaf per 18) 5323 / 5336, 256 5147 / 4906; 2^24 is a
+// tie from N_crit 256 on.
+constexpr size_t kRoundsKeys = size_t{1} << 25;
+bool direct_pays(size_t n, size_t nl0) { return nl0 <= 1 || n < kRoundsKeys || nl0 >= n / 32; }
+
 size_t nodes_of(size_t nl) { return nl + (nl ? (nl - 1) / 7 : 0); }
 
 __global__ void clear_word_kernel(uint32_t* w) { *w = 0; }
@@ -246,8 +256,9 @@ cstone_status cstone_build(const double* x, const double* y, const double* z, si
         // it then sees one listed, and the tree once more; from kListMaxKeys on,
         // where the launches no longer show, and where the tree's workspace
         // would overwrite the list, they are always enqueued.
+        const bool direct = tree_possible(n, max_iters) && direct_pays(n, nl);
         const uint32_t* listed = nullptr;
-        if (n && n < kListMaxKeys && tree_possible(n, max_iters) &&
+        if (n && n < kListMaxKeys && direct &&
             tree_workspace_bytes(n, n_crit, leaf_capacity, nl > 1) <= sort_scratch_bytes(n))
             listed = sort_listed_word(stage_ws, n, variant);
         // the sort reports a failed device-side wait into the same flag word
@@ -257,7 +268,7 @@ cstone_status cstone_build(const double* x, const double* y, const double* z, si
         if (mark(2) != hipSuccess) { s = CSTONE_ERR_DEVICE; break; }
         if (nl == 0) nl = 1;  // start from the root leaf {0, 8^L}
         bool done = false;
-        if (tree_possible(n, max_iters)) {  // tree and links are enqueued together, and the host looks once
+        if (direct) {  // tree and links are enqueued together, and the host looks once
             TreePass tree;
             if (tree.run(sorted_keys, n, n_crit, leaves, nl, leaf_capacity, counts, node_keys, child, level_offsets,
                          stage_ws, stage_bytes, tree_state, flag, listed, stream)) {

@@ -281,13 +281,17 @@ cstone_status run_global_rebalance(const uint64_t* P, const uint64_t* shard_off_
 }
 
 // The focused tree comes from the sorted keys directly (tree.hip), if so many
-// rounds are allowed and n is at most kFocusDirect: one pass over the keys, 16
-// B a particle, replaces the rounds' searches, launches and waits for the host.
-// 4 M Plummer particles, N_crit 32, one of 64 ranges, with links and the nodes'
-// MAC: 1000 -> 200 us. A round takes about 100 us whatever n, the pass some 3 us
-// per million particles, so from a tree that one round adapts it is not the
-// faster one above some 30 M, and from the root (8 to 10 rounds) not above 300 M.
-constexpr size_t kFocusDirect = size_t{1} << 25, kFocusDirectRoot = size_t{1} << 27;
+// rounds are allowed: one pass over the keys replaces the rounds' searches,
+// launches and waits for the host. 4 M Plummer particles, N_crit 32, one of 64
+// ranges, with links and the nodes' MAC: 1000 -> 200 us. From the root (5 to 15
+// rounds) it is the faster one at least to 2^26 keys (Plummer, N_crit 16: 936
+// against 1784 us). From another tree it takes a round to see that nothing has
+// changed and two for a little, whatever n; direct against rounds in us, unchanged
+// / changed: 2^18 Plummer keys, N_crit 16: 216 / 217 against 169 / 307, 2^20 232 /
+// 233 against 165 / 295, 2^22 272 / 275 against 176 / 314, 2^24 472 / 472 against
+// 188 / 336; N_crit 1000: 2^20 168 / 171 against 158 / 273, 2^24 336 / 332 against
+// 175 / 313.
+constexpr size_t kFocusDirect = size_t{1} << 21, kFocusDirectRoot = size_t{1} << 27;
 
 namespace {
 size_t focus_rounds_bytes(size_t leaf_capacity) {

@@ -588,11 +588,32 @@ cstone_status RebalanceLoop::wait(bool* finished) {
     return status;
 }
 
+namespace {
+
+// Whether the tree straight from the keys is the faster one: it reads all keys
+// and compares the arrays, whatever there is to change, while a round goes by the
+// leaves alone. From the root it always is (2^17 .. 2^27 keys, N_crit 16 .. 1 M:
+// 0.2 to 1 of the rounds' time, but 1.5 for uniform ones at 2^27 and N_crit from
+// 1000 on). From another array, direct against rounds in us, for a tree that stays
+// as it is / changes a little / is far off: 2^18 keys, N_crit 16: 79 / 87 / 86
+// against 96 / 106 / 110; 2^20: 113 / 115 / 116 against 87 / 100 / 102; 2^24, N_crit
+// 256: 138 / 139 / 139 against 111 / 110 / 112; 2^27: 596 / 597 / 602 against 326 /
+// 325 / 364, and N_crit 10^5 218 against 87. With many leaves the rounds' searches
+// cost as much: 2^27, N_crit 16, a leaf per 8 keys: 1013 / 1023 / 1072 against 934 /
+// 1157 / 4311.
+constexpr size_t kDirectKeys = size_t{1} << 18;
+constexpr size_t kDirectManyKeys = size_t{1} << 24;
+bool direct_pays(size_t n, size_t nl0) {
+    return nl0 == 1 || n <= kDirectKeys || (n >= kDirectManyKeys && nl0 >= n / 8);
+}
+
+}  // namespace
+
 cstone_status run_rebalance(const uint64_t* P, size_t n, uint32_t n_crit, uint64_t* leaves, size_t* n_leaves,
                             size_t cap, uint32_t* counts, uint32_t max_iters, uint32_t* iters_done, void* ws,
                             size_t ws_bytes, hipStream_t stream) {
     cstone_status s;
-    if (tree_possible(n, max_iters)) {
+    if (tree_possible(n, max_iters) && direct_pays(n, *n_leaves)) {
         TreePass tree;
         if (tree.run(P, n, n_crit, leaves, *n_leaves, cap, counts, nullptr, nullptr, nullptr, ws, ws_bytes, nullptr,
                      nullptr, nullptr, stream)) {
