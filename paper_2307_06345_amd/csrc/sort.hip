@@ -1336,10 +1336,12 @@ constexpr int kNumVariants = sizeof(kVariants) / sizeof(kVariants[0]);
 // 1500 Plummer particles 109 / 98 / 93 us, uniform ones 65,536 116 / 106 / 104,
 // 2^18 133 / 125 / 120, 591,351 145 / 140 / 145, 2^20 171 / 167 / 178, 2^21 196
 // / 196 / 224. By turns with the 512 x 16 tiles on fresh inputs: 1500 105 -> 94
-// us, 65,536 117 -> 111, 591,351 Plummer 183 both.
+// us, 65,536 117 -> 111, 591,351 Plummer 183 both. Sorts alone with 512 x 16 / 8,
+// uniform: 2^20 + 5 116.9 / 111.8 us, 1.25 M 126.9 / 118.5, 1.5 M 127.3 / 122.7, 1.75
+// M 128.2 / 129.2; Plummer ones alike, their builds by 1 to 6 us.
 constexpr int kBuiltinVariant = 0;
 constexpr int kSmallVariant = 9, kMediumVariant = 10;
-constexpr size_t kSmallSort = size_t{1} << 18, kMediumSort = size_t{1} << 20;
+constexpr size_t kSmallSort = size_t{1} << 18, kMediumSort = size_t{3} << 19;
 static_assert(kVariants[kSmallVariant].items == 4 && kVariants[kMediumVariant].items == 8, "the small tiles");
 
 // Split sorts of particle keys: 9-bit digits, the top three first (the

@@ -42,3 +42,19 @@ def test_small_shapes_by_table(n, shape):
         cs.tune_set(cs.TUNE_SORT, n, -1)
     assert np.array_equal(cs.to_numpy(P), rP)
     assert np.array_equal(cs.to_numpy(perm), rperm)
+
+
+@pytest.mark.parametrize("n", [(3 << 19) - 1, 3 << 19, (3 << 19) + 1])
+@pytest.mark.parametrize("kind", ["uniform", "crowded"])
+def test_sort_beside_the_upper_line(n, kind):
+    """The line between the middle and the largest shape, with and without the extra digit."""
+    rng = np.random.default_rng(n)
+    keys = rng.integers(0, 1 << 63, n, dtype=np.uint64)
+    if kind == "crowded":
+        core = rng.choice(1 << 27, n // 200, replace=False).astype(np.uint64) << np.uint64(36)
+        keys = core[rng.integers(0, core.size, n)] | (keys & np.uint64((1 << 36) - 1))
+    print("[case] sort shape, upper line", n, kind, flush=True)
+    P, perm = cs.sort(cs.from_numpy(keys, "cuda"))
+    rP, rperm = oracle.sort(keys)
+    assert np.array_equal(cs.to_numpy(P), rP)
+    assert np.array_equal(cs.to_numpy(perm), rperm)
