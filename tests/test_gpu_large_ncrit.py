@@ -14,6 +14,7 @@ pytestmark = pytest.mark.gpu
 
 cs = pytest.importorskip("paper_2307_06345_amd")
 
+
 def eq(got, ref, what):
     a = cs.to_numpy(got)
     assert a.shape == ref.shape and np.array_equal(a, ref), what
