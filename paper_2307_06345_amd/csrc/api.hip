@@ -31,6 +31,12 @@ constexpr size_t kListMaxKeys = size_t{1} << 25;
 constexpr size_t kRoundsKeys = size_t{1} << 25;
 bool direct_pays(size_t n, size_t nl0) { return nl0 <= 1 || n < kRoundsKeys || nl0 >= n / 32; }
 
+// What a build's stages hand on besides their arrays.
+struct BuildWords {
+    TreeState tree;  // cleared by the sort's set-up
+    uint32_t flag;   // non-finite coordinates; the sort's errors
+};
+
 size_t nodes_of(size_t nl) { return nl + (nl ? (nl - 1) / 7 : 0); }
 
 __global__ void clear_word_kernel(uint32_t* w) { *w = 0; }
@@ -174,12 +180,11 @@ cstone_status cstone_gather_xyz_packed(const double* x, const double* y, const d
 size_t cstone_build_workspace_bytes(size_t n, size_t leaf_capacity) {
     Carve c(nullptr);
     c.take<uint64_t>(n);  // unsorted keys
-    c.take<uint32_t>(1);  // non-finite flag
-    c.take<TreeState>(1);  // cleared by the sort's set-up
+    c.take<BuildWords>(1);
     // the sort runs before the loop; the loop and the link share the stream
     // without a host check in between, so they get separate parts (the split
     // list of the loop is largest for n_crit = 1)
-    size_t stage = std::max(sort_workspace_bytes(n, true),
+    size_t stage = std::max(prepared_sort_workspace_bytes(n),
                             rebalance_workspace_bytes(n, 1, leaf_capacity) + link_workspace_bytes(leaf_capacity));
     return c.off + stage;
 }
@@ -199,8 +204,9 @@ cstone_status cstone_build(const double* x, const double* y, const double* z, si
 
     Carve c(ws);
     uint64_t* keys = c.take<uint64_t>(n);
-    uint32_t* flag = c.take<uint32_t>(1);
-    TreeState* tree_state = c.take<TreeState>(1);
+    BuildWords* words = c.take<BuildWords>(1);
+    uint32_t* flag = &words->flag;
+    TreeState* tree_state = &words->tree;
     // the sort shape is looked up once: the key kernel's digit counts, the
     // sort's set-up and its passes must all use the same one
     const int variant = sort_resolve_variant(n);

@@ -577,7 +577,7 @@ ShardedWs carve_sharded(void* ws, size_t n, size_t max_shard, size_t cap, uint32
     w.all_perm = one.take<uint32_t>(n);
     w.rows = one.take<uint32_t>(static_cast<size_t>(G) * ((n + kShardTile - 1) / kShardTile));
     w.totals = one.take<uint32_t>(G);
-    w.all_stage_bytes = std::max(sort_workspace_bytes(n, true), n && cap ? tree_workspace_bytes(n, 1, cap, true) : 0);
+    w.all_stage_bytes = std::max(prepared_sort_workspace_bytes(n), n && cap ? tree_workspace_bytes(n, 1, cap, true) : 0);
     w.all_stage = one.take<char>(w.all_stage_bytes);
     w.all_bytes = one.off;
     return w;

@@ -26,6 +26,7 @@ cstone_status launch_keys(const double* x, const double* y, const double* z, siz
 // sorted on. Particle keys with a permutation take the split path (top two
 // digits, then every bucket on its own), other sorts plain LSD passes.
 size_t sort_workspace_bytes(size_t n, bool with_perm);
+size_t prepared_sort_workspace_bytes(size_t n);  // with a perm, set up by sort_setup_from_keys
 // pass_events: NULL, or sort_passes() + 1 events recorded before the first
 // pass and after every pass (split path: after the first top pass, after the
 // last one, after the bucket sort and after the low passes). prepared: the key

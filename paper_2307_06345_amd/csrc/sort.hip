@@ -1373,10 +1373,11 @@ struct SortWs {
     uint32_t* large_start;
     uint32_t* large_hist;
     size_t max_buckets, max_tiles_any;
-    // per-block first-digit counts and flags of a build's key kernel
+    size_t bytes;
+    // per-block digit counts and flags of a build's key kernel, past what a sort alone needs
     uint32_t* key_parts;
     uint32_t* key_bad;
-    size_t bytes;
+    size_t prepared_bytes;
 };
 
 SortWs carve_sort(void* ws, size_t n, bool with_perm) {
@@ -1399,10 +1400,13 @@ SortWs carve_sort(void* ws, size_t n, bool with_perm) {
         s.large_tiles = c.take<uint4>(s.max_tiles_any);
         s.large_start = c.take<uint32_t>(s.max_buckets + 1);
         s.large_hist = c.take<uint32_t>((s.max_buckets + 1) * kLowPasses * kMaxRadix);
+    }
+    s.bytes = c.off;
+    if (with_perm) {
         s.key_parts = c.take<uint32_t>(static_cast<size_t>(kKeyBlocksMax) * kKeyDigitsMax * kMaxRadix);
         s.key_bad = c.take<uint32_t>(kKeyBlocksMax);
     }
-    s.bytes = c.off;
+    s.prepared_bytes = c.off;
     return s;
 }
 
@@ -1414,6 +1418,8 @@ bool use_split(size_t n, int sig_bits, bool with_perm, const Variant& var) {
 }  // namespace
 
 size_t sort_workspace_bytes(size_t n, bool with_perm) { return carve_sort(nullptr, n, with_perm).bytes; }
+
+size_t prepared_sort_workspace_bytes(size_t n) { return carve_sort(nullptr, n, true).prepared_bytes; }
 
 int sort_builtin_variant(size_t n) { return n <= kSmallSort ? kSmallVariant : n <= kMediumSort ? kMediumVariant : kBuiltinVariant; }
 
