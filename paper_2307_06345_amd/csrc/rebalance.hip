@@ -485,8 +485,12 @@ cstone_status launch_node_counts(const uint64_t* sorted_keys, size_t n, const ui
     return CSTONE_OK;
 }
 
+size_t rebalance_rounds_bytes(size_t n, uint32_t n_crit, size_t leaf_capacity) {
+    return carve_rebalance(nullptr, n, n_crit ? n_crit : 1, leaf_capacity).bytes;
+}
+
 size_t rebalance_workspace_bytes(size_t n, uint32_t n_crit, size_t leaf_capacity) {
-    return std::max(carve_rebalance(nullptr, n, n_crit ? n_crit : 1, leaf_capacity).bytes,
+    return std::max(rebalance_rounds_bytes(n, n_crit, leaf_capacity),
                     leaf_capacity ? tree_workspace_bytes(n, n_crit ? n_crit : 1, leaf_capacity) : 0);
 }
 
@@ -613,6 +617,7 @@ cstone_status run_rebalance(const uint64_t* P, size_t n, uint32_t n_crit, uint64
                             size_t cap, uint32_t* counts, uint32_t max_iters, uint32_t* iters_done, void* ws,
                             size_t ws_bytes, hipStream_t stream) {
     cstone_status s;
+    if (ws_bytes < rebalance_rounds_bytes(n, n_crit, cap)) return CSTONE_ERR_INVALID_ARG;  // what both ways need
     if (tree_possible(n, max_iters) && direct_pays(n, *n_leaves)) {
         TreePass tree;
         if (tree.run(P, n, n_crit, leaves, *n_leaves, cap, counts, nullptr, nullptr, nullptr, ws, ws_bytes, nullptr,
