@@ -133,13 +133,15 @@ CSTONE_API cstone_status cstone_node_counts(const uint64_t* sorted_keys, size_t 
  *   max_iters    rounds allowed (0 means 22 = L + 1)
  *   iters_done   host, rounds run (a round is one f + one g), or NULL
  *   ws           device workspace of cstone_rebalance_workspace_bytes(n, n_crit,
- *                leaf_capacity) bytes
+ *                leaf_capacity) bytes; with the _least_ size the outputs are the
+ *                same, but the tree may have to come round by round
  * Synchronises `stream`. Errors: INVALID_ARG; CAPACITY (leaves keep the last
  * array that fitted, *n_leaves is the count the next round needed);
  * NOT_CONVERGED (leaves hold the array after max_iters rounds, a valid
  * cornerstone array); DEVICE.
  */
 CSTONE_API size_t cstone_rebalance_workspace_bytes(size_t n, uint32_t n_crit, size_t leaf_capacity);
+CSTONE_API size_t cstone_rebalance_least_workspace_bytes(size_t n, uint32_t n_crit, size_t leaf_capacity);
 CSTONE_API cstone_status cstone_rebalance(const uint64_t* sorted_keys, size_t n, uint32_t n_crit, uint64_t* leaves,
                                size_t* n_leaves, size_t leaf_capacity, uint32_t* counts,
                                uint32_t max_iters, uint32_t* iters_done, void* ws, size_t ws_bytes,
@@ -346,7 +348,10 @@ CSTONE_API cstone_status cstone_gather_xyz_packed(const double* x, const double*
  * cstone_build_sharded: keys of every particle (Sec. 3), every shard's keys
  * sorted (sorted_keys and perm per shard, perm relative to the shard's first
  * particle), and what cstone_global_rebalance makes of `leaves` (e.g. the root
- * {0, 8^L}), for up to 64 shards out of one sort of all keys. ws: cstone_build_sharded_workspace_bytes (0 for bad offsets).
+ * {0, 8^L}), for up to 64 shards out of one sort of all keys. ws:
+ * cstone_build_sharded_workspace_bytes (0 for bad offsets); with the _least_
+ * size (2.2 to 2.5 times less from 2 shards on) the outputs are the same, but
+ * the shards are sorted one after another.
  * Errors as cstone_build (no linking: cstone_link_octree on the result).
  *
  * cstone_sfc_partition: groups the leaves into n_ranks bins of consecutive
@@ -366,6 +371,8 @@ CSTONE_API cstone_status cstone_global_rebalance(const uint64_t* sorted_keys, co
                                                  hipStream_t stream);
 CSTONE_API size_t cstone_build_sharded_workspace_bytes(const uint64_t* shard_offsets, uint32_t n_shards,
                                                        size_t leaf_capacity);
+CSTONE_API size_t cstone_build_sharded_least_workspace_bytes(const uint64_t* shard_offsets, uint32_t n_shards,
+                                                             size_t leaf_capacity);
 CSTONE_API cstone_status cstone_build_sharded(const double* x, const double* y, const double* z,
                                               const uint64_t* shard_offsets, uint32_t n_shards,
                                               const cstone_box* box, cstone_curve curve, uint32_t n_crit,
@@ -400,7 +407,8 @@ CSTONE_API cstone_status cstone_sfc_partition(const uint32_t* counts, size_t n_l
  * focus_end <= 8^L. Synchronises `stream` once; once per round where max_iters
  * is below L + 1, a round exceeds the capacity or n is above 2^21 (from the root
  * 2^27).
- * ws: cstone_focus_rebalance_workspace_bytes(leaf_capacity).
+ * ws: cstone_focus_rebalance_workspace_bytes(leaf_capacity), or the _least_ size
+ * as in cstone_rebalance.
  *
  * cstone_focus_mac (f^LE_2): fails[p] = 1 if node p of a linked octree (NK,
  * placeholder-bit keys, device, n_nodes uint64) fails the MAC against F, else
@@ -408,6 +416,7 @@ CSTONE_API cstone_status cstone_sfc_partition(const uint32_t* counts, size_t n_l
  * ws: cstone_focus_mac_workspace_bytes().
  */
 CSTONE_API size_t cstone_focus_rebalance_workspace_bytes(size_t leaf_capacity);
+CSTONE_API size_t cstone_focus_rebalance_least_workspace_bytes(size_t leaf_capacity);
 CSTONE_API cstone_status cstone_focus_rebalance(const uint64_t* sorted_keys, size_t n, uint32_t n_crit,
                                                 cstone_curve curve, uint64_t focus_start, uint64_t focus_end,
                                                 double theta, uint64_t* leaves, size_t* n_leaves,

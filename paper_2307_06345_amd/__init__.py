@@ -78,6 +78,7 @@ def _load() -> ctypes.CDLL:
         "cstone_sort": (i32, [P, P, P, sz, P, sz, P]),
         "cstone_node_counts": (i32, [P, sz, P, sz, P, P]),
         "cstone_rebalance_workspace_bytes": (sz, [sz, u32, sz]),
+        "cstone_rebalance_least_workspace_bytes": (sz, [sz, u32, sz]),
         "cstone_rebalance": (i32, [P, sz, u32, P, psz, sz, P, u32, pu32, P, sz, P]),
         "cstone_leaf_capacity_bound": (sz, [sz, u32, sz]),
         "cstone_node_count": (sz, [sz]),
@@ -104,8 +105,10 @@ def _load() -> ctypes.CDLL:
         "cstone_global_rebalance_workspace_bytes": (sz, [sz, u32]),
         "cstone_global_rebalance": (i32, [P, P, u32, u32, P, psz, sz, P, u32, pu32, P, sz, P]),
         "cstone_build_sharded_workspace_bytes": (sz, [P, u32, sz]),
+        "cstone_build_sharded_least_workspace_bytes": (sz, [P, u32, sz]),
         "cstone_build_sharded": (i32, [P, P, P, P, u32, pbox, i32, u32, P, P, P, psz, sz, P, u32, pu32, P, sz, P]),
         "cstone_focus_rebalance_workspace_bytes": (sz, [sz]),
+        "cstone_focus_rebalance_least_workspace_bytes": (sz, [sz]),
         "cstone_focus_rebalance": (i32, [P, sz, u32, i32, ctypes.c_uint64, ctypes.c_uint64, ctypes.c_double, P, psz, sz,
                                          P, u32, pu32, P, sz, P]),
         "cstone_focus_mac_workspace_bytes": (sz, []),
@@ -167,6 +170,17 @@ def _dev(t: torch.Tensor, dtype) -> torch.Tensor:
 
 def _workspace(nbytes: int, device) -> torch.Tensor:
     return torch.empty(max(int(nbytes), 256), dtype=torch.uint8, device=device)
+
+
+def _workspace_or(nbytes: int, least: int, device) -> torch.Tensor:
+    """A workspace of nbytes or, where memory is short, of the least that the
+    call runs with."""
+    try:
+        return _workspace(nbytes, device)
+    except torch.OutOfMemoryError:
+        if least >= nbytes:
+            raise
+        return _workspace(least, device)
 
 
 def to_numpy(t: torch.Tensor) -> np.ndarray:
@@ -253,9 +267,10 @@ def rebalance(sorted_keys, n_crit: int, leaves=None, capacity=None, max_iters: i
     if leaves is not None:
         buf[: nl0 + 1].copy_(leaves)
     counts = torch.empty(capacity, dtype=torch.int32, device=dev)
-    need = _lib.cstone_rebalance_workspace_bytes(n, int(n_crit), capacity)
     if ws is None:
-        ws = _workspace(need, dev)
+        size = (n, int(n_crit), capacity)
+        ws = _workspace_or(_lib.cstone_rebalance_workspace_bytes(*size),
+                           _lib.cstone_rebalance_least_workspace_bytes(*size), dev)
     nl = ctypes.c_size_t(nl0)
     rounds = ctypes.c_uint32(0)
     st = _lib.cstone_rebalance(_ptr(sorted_keys), n, int(n_crit), _ptr(buf), ctypes.byref(nl), capacity, _ptr(counts),
@@ -397,9 +412,10 @@ def _offsets(shard_offsets):
 
 def build_sharded(x, y, z, shard_offsets, box, curve, n_crit: int, capacity=None, max_iters: int = 0, stream=None):
     """Sec. 6 on one device: particles split into shards at `shard_offsets`
-    (n_shards + 1 ints), each shard's keys sorted on their own, the tree of all
-    particles from per-shard counts summed every round. Returns (sorted keys
-    per shard, perm per shard, K, summed counts, rounds)."""
+    (n_shards + 1 ints), each shard's keys sorted (up to 64 shards out of one
+    sort of all keys, memory permitting, else one after another) and the tree
+    of all particles. Returns (sorted keys per shard, perm per shard, K, summed
+    counts, rounds)."""
     n = x.numel()
     for t in (x, y, z):
         _dev(t, torch.float64)
@@ -412,7 +428,8 @@ def build_sharded(x, y, z, shard_offsets, box, curve, n_crit: int, capacity=None
     K = torch.empty(capacity + 1, dtype=torch.int64, device=dev)
     K[:2].copy_(torch.tensor([0, -(1 << 63)], dtype=torch.int64))  # the root {0, 8^L}
     counts = torch.empty(capacity, dtype=torch.int32, device=dev)
-    ws = _workspace(_lib.cstone_build_sharded_workspace_bytes(off_p, G, capacity), dev)
+    ws = _workspace_or(_lib.cstone_build_sharded_workspace_bytes(off_p, G, capacity),
+                       _lib.cstone_build_sharded_least_workspace_bytes(off_p, G, capacity), dev)
     nl = ctypes.c_size_t(1)
     rounds = ctypes.c_uint32(0)
     b = Box.of(box)
@@ -464,7 +481,8 @@ def focus_rebalance(sorted_keys, n_crit: int, curve: int, focus_start: int, focu
     else:
         K[: nl0 + 1].copy_(leaves)
     counts = torch.empty(capacity, dtype=torch.int32, device=dev)
-    ws = _workspace(_lib.cstone_focus_rebalance_workspace_bytes(capacity), dev)
+    ws = _workspace_or(_lib.cstone_focus_rebalance_workspace_bytes(capacity),
+                       _lib.cstone_focus_rebalance_least_workspace_bytes(capacity), dev)
     nl = ctypes.c_size_t(nl0)
     rounds = ctypes.c_uint32(0)
     st = _lib.cstone_focus_rebalance(_ptr(sorted_keys), n, int(n_crit), int(curve), int(focus_start), int(focus_end),

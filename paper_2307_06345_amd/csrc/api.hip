@@ -83,6 +83,10 @@ size_t cstone_rebalance_workspace_bytes(size_t n, uint32_t n_crit, size_t leaf_c
     return rebalance_workspace_bytes(n, n_crit, leaf_capacity);
 }
 
+size_t cstone_rebalance_least_workspace_bytes(size_t n, uint32_t n_crit, size_t leaf_capacity) {
+    return rebalance_rounds_bytes(n, n_crit, leaf_capacity);
+}
+
 size_t cstone_leaf_capacity_bound(size_t n, uint32_t n_crit, size_t n_leaves_start) {
     const size_t full = n / (static_cast<size_t>(n_crit) + 1);
     size_t bound = 7 * static_cast<size_t>(kL) * full + 1;

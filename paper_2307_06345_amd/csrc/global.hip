@@ -308,13 +308,11 @@ cstone_status run_global_rebalance(const uint64_t* P, const uint64_t* shard_off_
 // 175 / 313.
 constexpr size_t kFocusDirect = size_t{1} << 21, kFocusDirectRoot = size_t{1} << 27;
 
-namespace {
 size_t focus_rounds_bytes(size_t leaf_capacity) {
     Carve c(nullptr);
     c.take<uint64_t>(2);
     return c.off + global_rebalance_workspace_bytes(leaf_capacity, 1);
 }
-}  // namespace
 
 size_t focus_workspace_bytes(size_t leaf_capacity) {
     return std::max(focus_rounds_bytes(leaf_capacity),
@@ -685,6 +683,13 @@ CSTONE_API size_t cstone_build_sharded_workspace_bytes(const uint64_t* shard_off
     return n_shards <= cs::kMaxPartShards ? std::max(w.bytes, w.all_bytes) : w.bytes;
 }
 
+CSTONE_API size_t cstone_build_sharded_least_workspace_bytes(const uint64_t* shard_offsets, uint32_t n_shards,
+                                                             size_t leaf_capacity) {
+    size_t mx = 0;
+    if (!shard_offsets || !cs::offsets_ok(shard_offsets, n_shards, shard_offsets[n_shards], &mx)) return 0;
+    return cs::carve_sharded(nullptr, shard_offsets[n_shards], mx, leaf_capacity, n_shards).bytes;
+}
+
 CSTONE_API cstone_status cstone_build_sharded(const double* x, const double* y, const double* z,
                                               const uint64_t* shard_offsets, uint32_t n_shards,
                                               const cstone_box* box, cstone_curve curve, uint32_t n_crit,
@@ -741,6 +746,10 @@ CSTONE_API cstone_status cstone_build_sharded(const double* x, const double* y, 
 
 CSTONE_API size_t cstone_focus_rebalance_workspace_bytes(size_t leaf_capacity) {
     return cs::focus_workspace_bytes(leaf_capacity);
+}
+
+CSTONE_API size_t cstone_focus_rebalance_least_workspace_bytes(size_t leaf_capacity) {
+    return cs::focus_rounds_bytes(leaf_capacity);
 }
 
 CSTONE_API cstone_status cstone_focus_rebalance(const uint64_t* sorted_keys, size_t n, uint32_t n_crit,

@@ -253,6 +253,7 @@ cstone_status launch_batch_tree(const uint64_t* P, size_t n_total, const BatchSe
 // rebalance.hip
 cstone_status launch_node_counts(const uint64_t* sorted_keys, size_t n, const uint64_t* leaves, size_t n_leaves,
                                  uint32_t* counts, hipStream_t stream);
+size_t rebalance_rounds_bytes(size_t n, uint32_t n_crit, size_t leaf_capacity);  // of the rounds alone
 size_t rebalance_workspace_bytes(size_t n, uint32_t n_crit, size_t leaf_capacity);
 
 constexpr int kMaxRounds = 64;

@@ -35,3 +35,40 @@ def test_a_short_workspace_of_a_rebalance_is_refused(leaves):
     p = ctypes.c_void_p(1 << 40)  # never touched
     nl = ctypes.c_size_t(leaves)
     assert lib.cstone_rebalance(p, n, n_crit, p, ctypes.byref(nl), cap, None, 0, None, p, need - 1, None) == 1
+
+
+class _Short:
+    """Stands for the allocator: nothing longer than `most` bytes is to be had."""
+
+    def __init__(self, most):
+        self.most, self.asked = most, []
+
+    def __call__(self, nbytes, device):
+        self.asked.append(nbytes)
+        if nbytes > self.most:
+            raise cs.torch.OutOfMemoryError("no memory")
+        return nbytes
+
+
+def test_a_shorter_workspace_where_memory_is_short(monkeypatch):
+    for most, got in ((1000, 800), (500, 300)):
+        short = _Short(most)
+        monkeypatch.setattr(cs, "_workspace", short)
+        assert cs._workspace_or(800, 300, "cpu") == got
+    for nbytes, least in ((800, 600), (800, 800), (600, 900)):
+        monkeypatch.setattr(cs, "_workspace", _Short(500))
+        with pytest.raises(cs.torch.OutOfMemoryError):
+            cs._workspace_or(nbytes, least, "cpu")
+
+
+def test_the_least_sizes_are_those_of_before():
+    """What the calls asked for when they went by rounds and shard by shard."""
+    import numpy as np
+    for G, before in ((1, 473180928), (2, 305285888), (8, 268500224)):
+        off = np.linspace(0, 1 << 24, G + 1).astype(np.uint64)
+        cap = 10 * (1 << 24) // 65 + 1024
+        p = off.ctypes.data_as(ctypes.c_void_p)
+        least = lib.cstone_build_sharded_least_workspace_bytes(p, G, cap)
+        assert 0 < least <= before < lib.cstone_build_sharded_workspace_bytes(p, G, cap)
+    assert lib.cstone_rebalance_least_workspace_bytes(1 << 24, 1000, 168628) <= 2845440
+    assert lib.cstone_focus_rebalance_least_workspace_bytes(1500) <= 43008
