@@ -603,7 +603,7 @@ def main():
                      "kernel_source_digest": digest},
         "build": {"stage_ms": {"keys": stage[0], "sort": stage[1], "rebalance": stage[2], "link": stage[3]},
                   "sort_pass_ms": passes,
-                  "sort_pass_names": (["top pass 1 (bits 36-44)", "top passes 2 and 3 (bits 45-62)", "buckets",
+                  "sort_pass_names": (["top pass 1 (bits 36-44; crowded keys: and 27-35)", "top passes 2 and 3 (bits 45-62)", "buckets",
                                        "low passes"] if split else [f"digit {i}" for i in range(len(passes))]),
                   "model_bytes": model,
                   "model_fraction": model["total"] / (ms_per_step * 1e-3) / (HBM_PEAK_GBS * 1e9),

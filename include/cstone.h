@@ -206,10 +206,13 @@ CSTONE_API cstone_status cstone_link_octree_by_sort(const uint64_t* leaves, size
 typedef struct cstone_timings {
     float stage_ms[4];     /* keys, sort, rebalance loop, link (the loop's time
                               holds the link's where the tree is written with
-                              its links, straight from the sorted keys) */
+                              its links, straight from the sorted keys, and that
+                              of a tree that buckets not yet sorted made
+                              useless; the host's look between is in none) */
     float sort_pass_ms[8]; /* the particle-key sort (4 entries): the first top
-                              pass, the two later top passes together, the
-                              bucket pass, the low passes */
+                              pass (with the digit below it, bits 27 to 35,
+                              where the keys crowd), the two later top passes
+                              together, the bucket pass, the low passes */
     uint32_t sort_passes;  /* entries of sort_pass_ms in use */
 } cstone_timings;
 
