@@ -210,8 +210,11 @@ __device__ __forceinline__ uint32_t mark_wave(const uint64_t* __restrict__ Ps, u
 }
 
 // FOCUS (one set): a tile has no slots of its own, since most hold none of the
-// few internal nodes; those that do take a run of the shared ones.
-template <bool BATCH, bool FOCUS>
+// few internal nodes; those that do take a run of the shared ones. KEEP: whether
+// the bytes are kept (a batch's sets differ in it; the branch costs 1 us in 33 for
+// 2^24 particles).
+enum class Keep { kNone, kBytes, kByCrit };
+template <bool BATCH, bool FOCUS, Keep KEEP>
 __global__ __launch_bounds__(kMarkBlock) void tree_mark_kernel(const uint64_t* __restrict__ P, TreeOne one,
                                                                const BatchSet* __restrict__ sets,
                                                                const uint32_t* __restrict__ tile_set, uint32_t n_tiles,
@@ -241,7 +244,7 @@ __global__ __launch_bounds__(kMarkBlock) void tree_mark_kernel(const uint64_t* _
     const uint32_t base = tile * kTreeTile;
     const uint32_t wbase = wave * kMarkItems * kWave;  // the wave's first place
     if (tid < kTreeLevels) sm.level[tid] = 0;
-    if (!FOCUS && tid == 0) {  // where a set ends, for those that go by their bytes
+    if (KEEP != Keep::kNone && tid == 0) {  // where a set ends, for those that go by their bytes
         if (tile == 0) below[0] = 0;
         if (gtile + 1 == n_tiles) below[n] = 0;
     }
@@ -252,8 +255,8 @@ __global__ __launch_bounds__(kMarkBlock) void tree_mark_kernel(const uint64_t* _
                     : mark_wave<false, bytes.value>(Ps, base, wbase, n, N, max_level, below, mylist);
     };
     uint32_t starts;
-    if constexpr (FOCUS)
-        starts = wave_starts(std::false_type{});
+    if constexpr (KEEP != Keep::kByCrit)
+        starts = wave_starts(std::bool_constant<KEEP == Keep::kBytes>{});
     else
         starts = N <= kByteMaxCrit ? wave_starts(std::true_type{}) : wave_starts(std::false_type{});
     if constexpr (FOCUS) {
@@ -459,6 +462,9 @@ __global__ __launch_bounds__(kWriteBlock) void tree_write_kernel(const uint64_t*
     const uint32_t tid = threadIdx.x, lane = lane_id();
     const uint32_t wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     const uint32_t gtile = blockIdx.x, part = blockIdx.y, parts = gridDim.y;
+    // Of keys that the sort has not finished only the state is written, to say so:
+    // the tree would be thrown away, and what it leaves out is not there to read.
+    const uint32_t unsorted = listed ? *listed : 0u;
     uint32_t s = 0, tile = gtile, tiles = n_tiles;
     TreeOne o = one;
     uint64_t node_off = 0;
@@ -521,9 +527,6 @@ __global__ __launch_bounds__(kWriteBlock) void tree_write_kernel(const uint64_t*
     }
     uint64_t* Ko = K + o.leaf_off;
     uint32_t* Co = counts ? counts + o.leaf_off : nullptr;
-    // Of keys that the sort has not finished only the state is written, to say so:
-    // the tree would be thrown away, and what it leaves out is not there to read.
-    const uint32_t unsorted = listed ? *listed : 0u;
     const bool fits = nl <= o.cap;
     if (tile == 0 && part == 0) {
         if constexpr (BATCH) {
@@ -572,6 +575,7 @@ __global__ __launch_bounds__(kWriteBlock) void tree_write_kernel(const uint64_t*
     const uint32_t c = lane & 7u, group = lane & ~7u;
     const uint32_t ua = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(below) & 7u);
     const uint64_t* words = reinterpret_cast<const uint64_t*>(below - ua);  // the bytes by aligned words
+    uint32_t next_base = part * kWave;
     for (uint32_t base = 0; base < here; base += kWave) {
         const bool in = base + lane < here;
         const uint64_t key = in ? In[list + base + lane] : 1ull;
@@ -591,7 +595,8 @@ __global__ __launch_bounds__(kWriteBlock) void tree_write_kernel(const uint64_t*
             if (lane == q) run += static_cast<uint32_t>(__popcll(m));
             left &= ~m;
         }
-        if (base / kWave % parts != part) continue;  // another block's chunk
+        if (base != next_base) continue;  // another block's chunk
+        next_base += parts * kWave;
         // index of the first child, and the node's own
         const uint32_t child = __shfl(lo, lq + 1, kWave) + 8u * rank;
         const uint32_t lo_own = __shfl(lo, lq, kWave);
@@ -991,7 +996,9 @@ bool TreePass::run(const uint64_t* P, size_t n, uint32_t n_crit, uint64_t* leave
     const uint32_t* no_table = nullptr;
     constexpr uint32_t max_level = kL - 1;
     uint64_t* K = incremental_ ? w.K_new : leaves;
-    const auto mark = focus ? tree_mark_kernel<false, true> : tree_mark_kernel<false, false>;
+    const auto mark = focus ? tree_mark_kernel<false, true, Keep::kNone>
+                            : (n_crit <= kByteMaxCrit ? tree_mark_kernel<false, false, Keep::kBytes>
+                                                      : tree_mark_kernel<false, false, Keep::kNone>);
     const auto write = focus ? tree_write_kernel<false, true> : tree_write_kernel<false, false>;
     const FocusSpec spec = focus ? *focus : FocusSpec{};
     hipLaunchKernelGGL(mark, dim3(tiles), dim3(kMarkBlock), 0, stream, P, one, no_sets, no_table, tiles, max_level,
@@ -1074,7 +1081,7 @@ cstone_status launch_batch_tree(const uint64_t* P, size_t n_total, const BatchSe
     const TreeResults res{rounds, set_flags, sort_err, results};
     if (tiles) {
         const bool scanned = max_tiles > kDirectTiles;
-        hipLaunchKernelGGL((tree_mark_kernel<true, false>), dim3(tiles), dim3(kMarkBlock), 0, stream, P, one, sets,
+        hipLaunchKernelGGL((tree_mark_kernel<true, false, Keep::kByCrit>), dim3(tiles), dim3(kMarkBlock), 0, stream, P, one, sets,
                            tile_set, tiles, max_level, w.below, w.inodes, w.ipos, w.tile_off, w.rows, reserved,
                            FocusSpec{});
         if (scanned)
