@@ -48,7 +48,12 @@ constexpr int kMarkBlock = 512;
 constexpr int kMarkItems = 8;
 constexpr uint32_t kTreeTile = kMarkBlock * kMarkItems;  // particles per tile of all three launches
 constexpr int kMarkWaves = kMarkBlock / kWave;
-constexpr uint32_t kByteMaxCrit = 256;  // N_crit up to which the write launch goes by the particles' bytes
+// N_crit up to which the write launch goes by the particles' bytes; above it the
+// bytes of 8 N particles are too many round trips, and all nodes are searched.
+// Builds of 2^24 Plummer particles by bytes / by searches: N_crit 200 742 / 733 us,
+// 256 741 / 730, 500 750 / 727, 1000 751 / 717; uniform 2^20, 256 169 / 161. (Both
+// take the same at 100.)
+constexpr uint32_t kByteMaxCrit = 128;
 constexpr size_t kBytesPad = 192;  // a byte after the last particle's, and what the last groups read past it
 
 // Leading octal digits two keys share, 0 .. 21. Keys are below 2^63, so the bits
@@ -330,7 +335,10 @@ __global__ __launch_bounds__(kMarkBlock) void tree_mark_kernel(const uint64_t* _
 
 constexpr int kScanBlock = 256;
 constexpr int kScanItems = 8;
-constexpr uint32_t kDirectTiles = 64;  // sets of at most this many tiles are summed by the write blocks themselves
+// Sets of at most this many tiles are summed by the write blocks themselves, which
+// spares small builds a launch (builds of 2^15 .. 2^20 particles by 16, 64 and 128:
+// within 2 us of each other, by turns).
+constexpr uint32_t kDirectTiles = 64;
 
 // Block (row, set): exclusive scan of one row of counts over the set's tiles, in place, and its total.
 template <bool BATCH>

@@ -1,8 +1,9 @@
-"""Large N_crit, against the CPU oracle: the waves of the tree's first pass that
-look at a few keys only (N_crit from 512, the particles of a wave, on), particle
-counts around N_crit and the waves' and tiles' edges, batches in which such sets
-stand beside others, and both sides of the lines between the direct tree and the
-rounds. All outputs are integers and must match exactly."""
+"""Large N_crit, against the CPU oracle: the line up to which nodes are read off
+bytes (128), the waves of the tree's first pass that look at a few keys only
+(N_crit from 512, the particles of a wave, on), particle counts around N_crit and
+the waves' and tiles' edges, batches in which such sets stand beside others, and
+both sides of the lines between the direct tree and the rounds. All outputs are
+integers and must match exactly."""
 import numpy as np
 import pytest
 import torch
@@ -29,7 +30,8 @@ def points(kind, n, seed):
     return x, y, z
 
 
-CASES = [("uniform", 511, 511), ("uniform", 513, 512), ("uniform", 1024, 512), ("uniform", 4096, 511), ("uniform", 4097, 513),
+CASES = [("uniform", 30000, 127), ("uniform", 30000, 128), ("uniform", 30000, 129), ("crowd", 70001, 129),
+         ("uniform", 511, 511), ("uniform", 513, 512), ("uniform", 1024, 512), ("uniform", 4096, 511), ("uniform", 4097, 513),
          ("uniform", 70001, 512), ("uniform", 70001, 1000), ("uniform", 300007, 4095), ("uniform", 300007, 30000),
          ("crowd", 5000, 512), ("crowd", 70001, 700), ("crowd", 300007, 600), ("crowd", 300007, 5000), ("crowd", 20000, 19999)]
 
