@@ -161,14 +161,18 @@ constexpr int kPackBlock = 256;
 constexpr uint32_t kPackTile = 1024;  // particles a block packs at a time
 constexpr uint32_t kPackNear = 1u << 15;
 
-// Whether perm scatters: more than a quarter of 64 pairs of neighbours spread
-// over it lie kPackNear (256 KB of an array, which L2 holds many times) or more
-// apart. Random input has nearly all of them apart, input in the order of an
-// earlier step next to none. The same for every wave.
+// Whether perm scatters: more than two fifths of 64 pairs of neighbours spread over
+// it lie kPackNear (256 KB of an array, which L2 holds many times) or more apart.
+// Random input has nearly all of them apart, input in the order of an earlier step
+// next to none. The same for every wave. In between, 2^24 particles by the arrays /
+// by records, us, with the share of pairs apart: places off by up to 8000 (0.00) 367
+// / 435, 16,000 (0.00) 486 / 469, 65,000 (0.24) 508 / 474, 130,000 (0.55) 517 / 480; a
+// tenth of them anywhere (0.19) 254 / 342, a fifth (0.36) 342 / 363, 0.3 (0.51) 431 /
+// 394, half (0.75) 608 / 458.
 __device__ __forceinline__ bool perm_scatters(const uint32_t* __restrict__ perm, uint32_t n) {
     const uint32_t i = lane_id() * (n / kWave);  // i + 1 < n
     const uint32_t a = perm[i], b = perm[i + 1];
-    return __popcll(__ballot((a > b ? a - b : b - a) >= kPackNear)) * 4 > kWave;
+    return __popcll(__ballot((a > b ? a - b : b - a) >= kPackNear)) * 5 > kWave * 2;
 }
 
 // rec[i] = {x[i], y[i], z[i]}, through LDS so that both sides are whole lines,
