@@ -91,9 +91,10 @@ CSTONE_API cstone_status cstone_compute_keys(const double* x, const double* y, c
  * values). Stable radix sort: keys_out[i] = keys_in[perm_out[i]], keys_out
  * non-decreasing, equal keys in ascending original index. Keys are particle
  * keys: 63 significant bits (bit 63 is not sorted on). Three digit passes
- * order the keys by their top 27 bits; the runs of one 27-bit prefix are then
- * sorted in place, in LDS, or by four passes over their low 36 bits if longer
- * than 2048 keys.
+ * order the keys by their top 27 bits (a fourth before them by the 9 bits below,
+ * from 2^20 keys on, where a sample says that many keys share their 27 but not
+ * those); the runs of one prefix are then sorted in place, in LDS, or by four
+ * passes over their low 36 bits if longer than 2048 keys.
  *   keys_in   device, n uint64 below 2^63 (not modified; may not alias the outputs)
  *   keys_out  device, n uint64;  perm_out  device, n uint32
  *   ws        device workspace of cstone_sort_workspace_bytes(n) bytes

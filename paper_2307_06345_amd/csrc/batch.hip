@@ -56,7 +56,7 @@ struct BatchWs {
     uint32_t* flags;     // per set, then the sort's device-wait error word
     uint32_t* reserved;  // per set: shared slots of its internal nodes in use; cleared with the flags
     uint64_t* keys;
-    void* stage;  // the sort's workspace, then the rebalance's and the link's
+    void* stage;  // the sort's workspace, then the tree pass's
     size_t stage_bytes;
     size_t bytes;
     size_t off_tiles, off_seg_base, off_tree, tables_end;  // byte offsets of the plan tables (sets start at 0)

@@ -207,12 +207,14 @@ size_t tree_workspace_bytes(size_t n, uint32_t n_crit, size_t cap, bool incremen
 // 0 or at least L + 1) and there are particles
 bool tree_possible(size_t n, uint32_t max_iters);
 
-// The whole rebalance loop of one set, and its links (unless node_keys is
-// NULL), enqueued without a host synchronisation.
 // Exclusive scan of each of n_rows rows in place, one block per row; totals: n_rows.
 void launch_row_scan(uint32_t* rows, uint32_t n_rows, uint32_t row_length, uint32_t* totals, hipStream_t stream);
+
 struct FocusSpec;
 size_t focus_tree_workspace_bytes(size_t n, size_t cap);
+
+// The whole rebalance loop of one set, and its links (unless node_keys is
+// NULL), enqueued without a host synchronisation.
 class TreePass {
 public:
     // From the root (nl0 == 1) or, with the rounds counted from it, from the
@@ -264,14 +266,14 @@ constexpr int kCounterWords = 32;
 
 // Device-side loop state: the part the host reads after a batch of rounds ...
 struct LoopHeader {
-    uint64_t nl[kMaxRounds + 1];    // leaves entering round r (batched: entries, closing keys included)
+    uint64_t nl[kMaxRounds + 1];    // leaves entering round r
     uint32_t changed[kMaxRounds];   // some O_i != 1 in round r
     uint32_t merged[kMaxRounds];    // some O_i == 0 in round r
     uint32_t over[kMaxRounds];      // a child of a leaf split in round r holds more than n_crit (and can split)
     uint32_t nsplit[kMaxRounds];    // split leaves listed in round r
     uint32_t err;
     uint32_t input_flags;  // copy of the caller's key-stage flag word
-    uint64_t final_nl;     // set by the finalize kernel: leaves (entries) of the result array
+    uint64_t final_nl;     // set by the finalize kernel: leaves of the result array
     uint32_t final_last;   // rounds behind it
     uint32_t final_code;   // 0 running, 1 converged, 2 capacity exceeded
 };

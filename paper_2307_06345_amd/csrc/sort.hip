@@ -697,7 +697,7 @@ __global__ __launch_bounds__(BLOCK, (kMinBlocks<BLOCK, ITEMS>)) void onesweep_li
 // ---- prefix split: the top digits, then every bucket on its own ---------------
 //
 // For particle keys the three most significant digits (27 bits: the level-9
-// octant of a key), or four where the keys crowd (see decide_depth), are sorted
+// octant of a key), or four where the keys crowd (see depth.hpp), are sorted
 // first, by onesweep passes. The keys then form runs of one prefix
 // ("buckets"), each still in input order. A block
 // owns the buckets that start in its chunk of kLocalChunk keys and sorts each

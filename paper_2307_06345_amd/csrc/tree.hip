@@ -19,7 +19,7 @@
 //          lies wholly before it and by as many as its path digits add up to.
 // The work after the first pass goes with the internal nodes, a seventh of the
 // leaves. Tiles are independent in every launch: a decoupled look-back instead
-// of the scan (one pass over P writing K) took 208 us against 27 + 5 + 23 us
+// of the scan (one pass over P writing K) took 208 us against 32 + 7 + 48 us
 // for 2^24 keys, at 33-80 ns per tile of polling between the XCDs.
 //
 // The rounds' count is known too: every round moves a leaf by one level at
@@ -444,7 +444,7 @@ constexpr int kWriteWaves = kWriteBlock / kWave;
 // waves do not wait for their searches.
 //
 // Bound: instructions (about 40 per node for the bytes, its lanes together),
-// and three dependent reads (list, bytes, keys of the children's starts); 24 B
+// and three dependent reads (list, bytes, keys of the children's starts); 26 B
 // of K, counts, NK and CO are written per leaf.
 template <bool BATCH, bool FOCUS>
 __global__ __launch_bounds__(kWriteBlock) void tree_write_kernel(const uint64_t* __restrict__ P, TreeOne one,
