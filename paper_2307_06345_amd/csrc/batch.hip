@@ -39,6 +39,7 @@ struct cstone_batch {
     uint64_t inode_slots = 0;
     uint64_t max_tree_tiles = 0;  // of one set
     bool empty_sets = false;      // some set holds no particle
+    uint32_t most_crit = 0;       // largest N_crit
     int variant = 0;
     uint32_t rounds = cs::kL + 1;
     hipGraph_t graph = nullptr;
@@ -146,7 +147,7 @@ cstone_status enqueue_build(const cstone_batch& p, const double* x, const double
             return st;
     }
     return launch_batch_tree(sorted_keys, p.n_total, w.sets, ns, w.tree_tile_set, p.tree_tile_set.size(), p.max_tree_tiles,
-                             p.empty_sets, p.inode_slots, p.rounds, w.flags, sort_err, w.reserved, leaves, counts,
+                             p.empty_sets, p.most_crit, p.inode_slots, p.rounds, w.flags, sort_err, w.reserved, leaves, counts,
                              node_keys, child, level_offsets, reinterpret_cast<BatchResult*>(results), w.stage,
                              w.stage_bytes, stream);
 }
@@ -214,6 +215,7 @@ CSTONE_API cstone_status cstone_batch_create(const cstone_set* sets, uint32_t n_
         p->tree_tile_set.insert(p->tree_tile_set.end(), b.tree_tiles, s);
         p->max_tree_tiles = std::max<uint64_t>(p->max_tree_tiles, b.tree_tiles);
         p->empty_sets = p->empty_sets || b.n == 0;
+        p->most_crit = std::max(p->most_crit, b.n_crit);
     }
     p->part_off.push_back(part);
     p->leaf_off.push_back(leaf);

@@ -243,10 +243,11 @@ private:
 };
 
 // All sets of a batch: trees, links and results. tile_set[t]: set of tile t;
-// max_tiles: tiles of the largest set; reserved: a zeroed word per set (shared slots in use).
+// max_tiles: tiles of the largest set; most_crit: the largest N_crit; reserved: a
+// zeroed word per set (shared slots in use).
 size_t batch_tree_workspace_bytes(size_t n_total, uint32_t n_sets, size_t n_tiles, size_t inode_slots);
 cstone_status launch_batch_tree(const uint64_t* P, size_t n_total, const BatchSet* sets, uint32_t n_sets, const uint32_t* tile_set,
-                                size_t n_tiles, size_t max_tiles, bool empty_sets, size_t inode_slots, uint32_t rounds,
+                                size_t n_tiles, size_t max_tiles, bool empty_sets, uint32_t most_crit, size_t inode_slots, uint32_t rounds,
                                 const uint32_t* set_flags, const uint32_t* sort_err, uint32_t* reserved,
                                 uint64_t* leaves, uint32_t* counts, uint64_t* node_keys, uint32_t* child,
                                 uint32_t* level_offsets, BatchResult* results, void* ws, size_t ws_bytes,

@@ -216,8 +216,8 @@ __device__ __forceinline__ uint32_t mark_wave(const uint64_t* __restrict__ Ps, u
 
 // FOCUS (one set): a tile has no slots of its own, since most hold none of the
 // few internal nodes; those that do take a run of the shared ones. KEEP: whether
-// the bytes are kept (a batch's sets differ in it; the branch costs 1 us in 33 for
-// 2^24 particles).
+// the bytes are kept (a batch's sets may differ in it; the branch costs 1 us in 33
+// for 2^24 particles).
 enum class Keep { kNone, kBytes, kByCrit };
 template <bool BATCH, bool FOCUS, Keep KEEP>
 __global__ __launch_bounds__(kMarkBlock) void tree_mark_kernel(const uint64_t* __restrict__ P, TreeOne one,
@@ -1076,7 +1076,7 @@ size_t batch_tree_workspace_bytes(size_t n_total, uint32_t n_sets, size_t tiles,
 }
 
 cstone_status launch_batch_tree(const uint64_t* P, size_t n_total, const BatchSet* sets, uint32_t n_sets, const uint32_t* tile_set,
-                                size_t n_tiles, size_t max_tiles, bool empty_sets, size_t inode_slots, uint32_t rounds,
+                                size_t n_tiles, size_t max_tiles, bool empty_sets, uint32_t most_crit, size_t inode_slots, uint32_t rounds,
                                 const uint32_t* set_flags, const uint32_t* sort_err, uint32_t* reserved,
                                 uint64_t* leaves, uint32_t* counts, uint64_t* node_keys, uint32_t* child,
                                 uint32_t* level_offsets, BatchResult* results, void* ws, size_t ws_bytes,
@@ -1089,7 +1089,9 @@ cstone_status launch_batch_tree(const uint64_t* P, size_t n_total, const BatchSe
     const TreeResults res{rounds, set_flags, sort_err, results};
     if (tiles) {
         const bool scanned = max_tiles > kDirectTiles;
-        hipLaunchKernelGGL((tree_mark_kernel<true, false, Keep::kByCrit>), dim3(tiles), dim3(kMarkBlock), 0, stream, P, one, sets,
+        const auto mark = most_crit <= kByteMaxCrit ? tree_mark_kernel<true, false, Keep::kBytes>
+                                                    : tree_mark_kernel<true, false, Keep::kByCrit>;
+        hipLaunchKernelGGL(mark, dim3(tiles), dim3(kMarkBlock), 0, stream, P, one, sets,
                            tile_set, tiles, max_level, w.below, w.inodes, w.ipos, w.tile_off, w.rows, reserved,
                            FocusSpec{});
         if (scanned)
