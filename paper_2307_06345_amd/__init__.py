@@ -172,15 +172,15 @@ def _workspace(nbytes: int, device) -> torch.Tensor:
     return torch.empty(max(int(nbytes), 256), dtype=torch.uint8, device=device)
 
 
-def _workspace_or(nbytes: int, least: int, device) -> torch.Tensor:
-    """A workspace of nbytes or, where memory is short, of the least that the
+def _workspace_or(nbytes: int, least, device) -> torch.Tensor:
+    """A workspace of nbytes or, where memory is short, of the least() that the
     call runs with."""
     try:
         return _workspace(nbytes, device)
     except torch.OutOfMemoryError:
-        if least >= nbytes:
+        if least() >= nbytes:
             raise
-        return _workspace(least, device)
+        return _workspace(least(), device)
 
 
 def to_numpy(t: torch.Tensor) -> np.ndarray:
@@ -270,7 +270,7 @@ def rebalance(sorted_keys, n_crit: int, leaves=None, capacity=None, max_iters: i
     if ws is None:
         size = (n, int(n_crit), capacity)
         ws = _workspace_or(_lib.cstone_rebalance_workspace_bytes(*size),
-                           _lib.cstone_rebalance_least_workspace_bytes(*size), dev)
+                           lambda: _lib.cstone_rebalance_least_workspace_bytes(*size), dev)
     nl = ctypes.c_size_t(nl0)
     rounds = ctypes.c_uint32(0)
     st = _lib.cstone_rebalance(_ptr(sorted_keys), n, int(n_crit), _ptr(buf), ctypes.byref(nl), capacity, _ptr(counts),
@@ -435,7 +435,7 @@ def build_sharded(x, y, z, shard_offsets, box, curve, n_crit: int, capacity=None
     K[:2].copy_(torch.tensor([0, -(1 << 63)], dtype=torch.int64))  # the root {0, 8^L}
     counts = torch.empty(capacity, dtype=torch.int32, device=dev)
     ws = _workspace_or(_lib.cstone_build_sharded_workspace_bytes(off_p, G, capacity),
-                       _lib.cstone_build_sharded_least_workspace_bytes(off_p, G, capacity), dev)
+                       lambda: _lib.cstone_build_sharded_least_workspace_bytes(off_p, G, capacity), dev)
     nl = ctypes.c_size_t(1)
     rounds = ctypes.c_uint32(0)
     b = Box.of(box)
@@ -488,7 +488,7 @@ def focus_rebalance(sorted_keys, n_crit: int, curve: int, focus_start: int, focu
         K[: nl0 + 1].copy_(leaves)
     counts = torch.empty(capacity, dtype=torch.int32, device=dev)
     ws = _workspace_or(_lib.cstone_focus_rebalance_workspace_bytes(capacity),
-                       _lib.cstone_focus_rebalance_least_workspace_bytes(capacity), dev)
+                       lambda: _lib.cstone_focus_rebalance_least_workspace_bytes(capacity), dev)
     nl = ctypes.c_size_t(nl0)
     rounds = ctypes.c_uint32(0)
     st = _lib.cstone_focus_rebalance(_ptr(sorted_keys), n, int(n_crit), int(curve), int(focus_start), int(focus_end),

@@ -54,11 +54,11 @@ def test_a_shorter_workspace_where_memory_is_short(monkeypatch):
     for most, got in ((1000, 800), (500, 300)):
         short = _Short(most)
         monkeypatch.setattr(cs, "_workspace", short)
-        assert cs._workspace_or(800, 300, "cpu") == got
+        assert cs._workspace_or(800, lambda: 300, "cpu") == got
     for nbytes, least in ((800, 600), (800, 800), (600, 900)):
         monkeypatch.setattr(cs, "_workspace", _Short(500))
         with pytest.raises(cs.torch.OutOfMemoryError):
-            cs._workspace_or(nbytes, least, "cpu")
+            cs._workspace_or(nbytes, lambda: least, "cpu")
 
 
 def test_the_least_sizes_are_those_of_before():
