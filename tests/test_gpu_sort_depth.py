@@ -63,3 +63,18 @@ def test_build_of_a_crowded_set(n):
     for name, got in (("P", r.sorted_keys), ("perm", r.perm), ("K", r.leaves), ("counts", r.counts), ("NK", r.node_keys),
                       ("CO", r.child), ("LO", r.level_offsets)):
         assert np.array_equal(cs.to_numpy(got), ref[name]), name
+
+
+def test_sort_of_crowded_keys_beyond_2_30():
+    """The extra digit with 64-bit look-back words, whose rows its pass and the
+    next one share; checked by what fixes a stable sort."""
+    from tests import device_checks as dc
+    n = (1 << 30) + 777
+    g = torch.Generator(device="cuda").manual_seed(31)
+    print("[case] crowded sort", n, flush=True)
+    core = torch.randint(0, 1 << 27, (n // 1000,), device="cuda", generator=g) << 36
+    keys = core[torch.randint(0, core.numel(), (n,), device="cuda", generator=g)]
+    keys |= torch.randint(0, 1 << 36, (n,), device="cuda", generator=g)
+    keys[:: 5] &= ~0xFFFFFF  # ties
+    P, perm = cs.sort(keys)
+    dc.check_sorted_perm(P, perm, n, keys)
