@@ -508,7 +508,7 @@ CSTONE_API cstone_status cstone_tune_load(const char* path);
  * results[s] receives leaf and node counts, rounds and a cstone_status (OK,
  * NONFINITE, CAPACITY, NOT_CONVERGED) for the set, or DEVICE in every set if
  * a device-side wait gave up (its arrays are then unreliable). With CAPACITY the
- * leaf count is what the set's tree needs (and its arrays are not written); the
+ * leaf count is what the set's tree needs (and its tree is not written); the
  * other sets do not depend on it. Look-back
  * passes take their tiles in the order their blocks start, so batches (and
  * single builds) on different streams of one device may run at the same
